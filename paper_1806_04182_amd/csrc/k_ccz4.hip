@@ -24,8 +24,6 @@
 // done; then the RK stage update writes the results.
 #include <utility>
 
-#include <algorithm>
-
 #include "k_common.h"
 
 namespace mol {
@@ -45,31 +43,47 @@ __device__ constexpr int SI(int i, int j)
 // Neighbour combinations along stride s: e_m = (u_m - u_0) + (u_-m - u_0),
 // o_m = u_m - u_-m (m = 1, 2, 3).  In these, 12 h D1 = 8 o1 - o2,
 // 12 h^2 D2 = 16 e1 - e2, the sixth-order dissipation stencil is
-// e3 - 6 e2 + 15 e1, and b times the lop-sided derivative (the b >= 0
+// K = e3 - 6 e2 + 15 e1, and b times the lop-sided derivative (the b >= 0
 // stencil reading i-1 .. i+3, its mirror for b < 0) is
-// b (o3/2 - 3 o2 + 21 o1/2) + |b| (e3/2 - 3 e2 + 15 e1/2), which needs no
-// branch on the sign of b.
+// b (o3/2 - 3 o2 + 21 o1/2) + (|b|/2) K, which needs no branch on the sign of
+// b and shares K with the dissipation.
 struct Axis {
     double e1, e2, e3, o1, o2, o3;
 };
-__device__ __forceinline__ Axis axis(const double* __restrict__ u, int s)
+// the combinations of the point t along an axis whose m-th neighbour is at
+// offset at(m)
+template <class At>
+__device__ __forceinline__ Axis axis(const double* __restrict__ t, At at)
 {
-    const double c = u[0];
+    const double c = t[0];
+    const double p1 = t[at(1)], m1 = t[at(-1)], p2 = t[at(2)], m2 = t[at(-2)], p3 = t[at(3)], m3 = t[at(-3)];
     Axis a;
-    a.e1 = (u[s] - c) + (u[-s] - c);
-    a.e2 = (u[2 * s] - c) + (u[-2 * s] - c);
-    a.e3 = (u[3 * s] - c) + (u[-3 * s] - c);
-    a.o1 = u[s] - u[-s];
-    a.o2 = u[2 * s] - u[-2 * s];
-    a.o3 = u[3 * s] - u[-3 * s];
+    a.e1 = (p1 - c) + (m1 - c);
+    a.e2 = (p2 - c) + (m2 - c);
+    a.e3 = (p3 - c) + (m3 - c);
+    a.o1 = p1 - m1;
+    a.o2 = p2 - m2;
+    a.o3 = p3 - m3;
     return a;
+}
+// 12 h D1 along the axis at, and (12 h)^2 times the mixed derivative along at
+// and the axis of constant stride sb
+template <class At>
+__device__ __forceinline__ double lds_d1(const double* __restrict__ t, At at)
+{
+    return 8.0 * (t[at(1)] - t[at(-1)]) - (t[at(2)] - t[at(-2)]);
+}
+template <class At>
+__device__ __forceinline__ double lds_mix(const double* __restrict__ t, At at, int sb)
+{
+    return 8.0 * (lds_d1(t + sb, at) - lds_d1(t - sb, at)) - (lds_d1(t + 2 * sb, at) - lds_d1(t - 2 * sb, at));
 }
 
 struct CczConst {
     double i12h;    // 1 / (12 h)
     double i12h2;   // 1 / (12 h^2)
     double i144h2;  // 1 / (144 h^2)
-    double ko;      // sigma / (64 h)
+    double koa;     // dissipation in the units of the advection sum: 12 h sigma / (64 h)
     double kz, kc, f0, f1, g, eta;
 };
 
@@ -83,22 +97,19 @@ constexpr int ORDER[NF] = {GT + 0, GT + 1, GT + 2,   GT + 3,   GT + 4,   GT + 5,
 // DMA) and loads staged through registers (MOL_CCZ4_DMA = 0), in which the
 // halo tile's rows are padded to a pitch of PX doubles: a wave reads 8 rows
 // of 8 doubles; with PX = 24 (= 8 mod 16 doubles) every group of rows served
-// in one LDS cycle starts on distinct banks.  There only the halo points a
-// field's stencils read are loaded (below); NR, the passes of a whole-box
-// load with 16 lanes per row, bounds the loads per thread and sizes the
-// staging registers.
-#ifndef MOL_CCZ4_PERSISTENT
-#define MOL_CCZ4_PERSISTENT 0
-#endif
+// in one LDS cycle starts on distinct banks.  There, as in the other path,
+// only the halo points a field's stencils read are loaded (below); NR, the
+// passes of a whole-box load with 16 lanes per row, bounds the loads per
+// thread and sizes the staging registers.
 #ifndef MOL_CCZ4_DMA
 #define MOL_CCZ4_DMA 1
 #endif
 
 typedef __attribute__((address_space(3))) void lds_void;
 
-// s_waitcnt immediate that waits until at most n vector-memory loads of this
-// wave are outstanding (expcnt and lgkmcnt left unconstrained)
-__device__ constexpr int vm_wait(int n) { return 0x0F70 | n; }
+// s_waitcnt immediate that waits for all vector-memory loads of this wave
+// (expcnt and lgkmcnt left unconstrained)
+constexpr int VM_WAIT = 0x0F70;
 
 // Workgroup barrier after this wave's LDS accesses have completed.  Unlike
 // __syncthreads() it does not wait for the wave's outstanding vector-memory
@@ -130,58 +141,72 @@ struct CczLds {
     static constexpr int TPE = 6 * TY + 6 * TX + 16, OPE = 4 * TY + 4 * TX;
     static constexpr int BE = TZ * TPE + 4 * OPE, NB = (BE + NT - 1) / NT;
     static_assert(NZ + NB <= NR, "reduced box does not fit the load pattern");
-    // Direct loads into LDS: the halo box in two buffers of rows of HX
-    // doubles at pitch HX, written by 16-byte LDS-DMA loads (a wave's load
-    // fills 64 consecutive 16-byte chunks, lane l the l-th) while the other
-    // buffer is read.  Each buffer holds the window from row G of the first
-    // plane to row G + TY - 1 of the last, the two planes being read only in
-    // the tile's columns: NCH chunks, NI loads per thread.
+    // Direct loads into LDS (16-byte LDS-DMA: a wave's load fills 64
+    // consecutive 16-byte slots, lane l the l-th).  The halo box is held
+    // as two arrays of rows of TX = 8 doubles at the same row strides, the
+    // inner row axis being the longer of the tile's y and z: the core (the
+    // tile's columns x0 .. x0 + 7 of every row, from the first to the last
+    // row some stencil reads) and the wings (x0 + 8 .. x0 + 11 in slots
+    // 0 .. 3 and x0 - 4 .. x0 - 1 in slots 4 .. 7, i.e. slot x mod 8, of the
+    // rows within reach 2).
+    // Why: what bounds the halo loads is the number of 128-byte lines they
+    // request of the L2 (with loads of the whole 14-wide box the L1 waited on
+    // pending lines 66% of the time; the kernel took 0.39 ms with them and
+    // 0.22 ms without at 96^3).  An interior row starts on a 64-byte boundary,
+    // so a core row is one line where a 14-wide row is two, and the rows that
+    // only y, z and yz stencils read need no wings: 136 lines per tile for a
+    // single-axis field and 200 for one with second derivatives instead of 268.
+    // Stage at 96^3 0.391 -> 0.365 ms, at 128^3 0.906 -> 0.836, at 48^3 46.3 ->
+    // 43.7 us (the whole-box window before, this layout after, same GPU).
+    // The rows being contiguous, a wave's reads along y and z are conflict
+    // free, and so are those along x, since a wing slot lies on the bank of
+    // the core slot it continues.
     static constexpr bool DMA = MOL_CCZ4_DMA;
-    static constexpr int CPR = HX / 2, C0 = G * CPR, NCH = ((HZ - 1) * HY + TY) * CPR;
-    static constexpr int NI = (NCH + NT - 1) / NT;
-    // loads per thread that every wave issues (the waves past the end of the
-    // window skip the last one)
-    static constexpr int NIW = (NI - 1) * NT + (NT - 64) < NCH ? NI : NI - 1;
-    static constexpr int NBUF = DMA ? MOL_CCZ4_NBUF : 1;
-    static_assert(NBUF >= 1 && NBUF <= 3 && (DMA || NBUF == 1), "one to three halo buffers");
-    static_assert(HX % 2 == 0, "halo rows must be whole 16-byte chunks");
+    static constexpr bool YIN = TY >= TZ;                      // y is the inner row axis
+    static constexpr int NIN = YIN ? TY : TZ, NOUT = YIN ? TZ : TY;  // tile rows along both
+    static constexpr int HIN = NIN + 2 * G, HOUT = NOUT + 2 * G;
+    // core rows run from row G of the first outer row line to row G + NIN - 1
+    // of the last; wing rows the same one line further in
+    static constexpr int CROW0 = G, NCROW = (HOUT - 1) * HIN + NIN;
+    static constexpr int WROW0 = HIN + G, NWROW = (HOUT - 3) * HIN + NIN;
+    static constexpr int NCH = 4 * (NCROW + NWROW), NI = (NCH + NT - 1) / NT;
+    static_assert(TX == 8, "rows of the direct loads are 8 doubles");
+    static_assert((NCROW - WROW0 + CROW0) % 2 == 0, "wing rows start on the bank of their core row");
     static constexpr int LB = DMA ? 2 * NCH : LV;  // doubles per halo buffer
 };
 
 // fields whose stencils read only along the axes through the point (first
 // derivatives, advection, dissipation): their halo corners are never read
-[[maybe_unused]] __device__ constexpr bool single_axis(int f)
+__device__ constexpr bool single_axis(int f)
 {
     return (f >= KH && f < GH + 3) || f == TH || (f >= BB && f < BB + 3);
 }
 
 // One tile of the stage: the right-hand side of every interior point of tile
-// tidx and its stage update.  buf: the halo tile of the field passing
-// through LDS; akx: advection + dissipation of every field.
+// tidx and its stage update.  buf, buf2: the halo of the field passing
+// through LDS and (LDS-DMA) of the next one; akx: advection + dissipation of
+// every field.
 template <int TX, int TY, int TZ, bool UPWIND>
 __device__ __forceinline__ void ccz4_tile(const StageArgs& a, const CczConst& C, int tidx, double* __restrict__ buf,
-                                          double* __restrict__ buf2, double* __restrict__ buf3,
-                                          double (*__restrict__ akx)[TX * TY * TZ])
+                                          double* __restrict__ buf2, double (*__restrict__ akx)[TX * TY * TZ])
 {
     using L = CczLds<TX, TY, TZ>;
     constexpr bool DMA = L::DMA;
-    constexpr int HY = L::HY, HZ = L::HZ, PX = DMA ? L::HX : L::PX, NT = L::NT, NR = L::NR;
+    constexpr int HY = L::HY, HZ = L::HZ, PX = L::PX, NT = L::NT, NR = L::NR;
 
     const Tile tile = a.tiles[tidx];
     const PatchDev P = a.patches[tile.patch];
-    const int tx = threadIdx.x, tz = threadIdx.z;
-    const int tid = tx + TX * ((int)threadIdx.y + TY * tz);
-    // With the halo rows at a pitch of 14 doubles, the two rows that one LDS
-    // cycle serves for a wave's 8 x 8 reads (lanes 16 m .. 16 m + 15) are
-    // rows y and y + 4, whose 64-byte segments fall on disjoint banks
-    const int ty = (DMA && TY == 8) ? (((int)threadIdx.y >> 1) | (((int)threadIdx.y & 1) << 2)) : (int)threadIdx.y;
+    const int tid = threadIdx.x + TX * ((int)threadIdx.y + TY * (int)threadIdx.z);
+    // a wave holds whole rows along the inner row axis
+    const int rin = (tid / TX) % L::NIN, rout = tid / (TX * L::NIN);
+    const int tx = tid % TX, ty = L::YIN ? rin : rout, tz = L::YIN ? rout : rin;
     const bool valid = tile.o[0] + tx < P.n[0] && tile.o[1] + ty < P.n[1] && tile.o[2] + tz < P.n[2];
     // halo tile origin = tile origin - 3 in interior coordinates = tile origin in ghosted coordinates
     const int64_t hbase = P.off + (int64_t)tile.o[2] * P.pitch_z + (int64_t)tile.o[1] * P.pitch_y + tile.o[0];
     const int64_t c = hbase + (int64_t)(tz + G) * P.pitch_z + (int64_t)(ty + G) * P.pitch_y + (tx + G);
     const int64_t fs = P.fs;
 
-    const int hzmax = P.n[2] + 2 * G - tile.o[2];  // halo planes inside the ghosted box
+    [[maybe_unused]] const int hzmax = P.n[2] + 2 * G - tile.o[2];  // halo planes inside the ghosted box
     double stg[NR];
     // the cross of a single-axis field (fewer loads than the box): z-slab
     // element tid + r NT is column (zx, zy) of plane zz + r ZPP; wing element
@@ -303,26 +328,49 @@ __device__ __forceinline__ void ccz4_tile(const StageArgs& a, const CczConst& C,
         }
     };
 
-    // LDS-DMA loads of the halo window: chunk j = r NT + tid, offsets from the
-    // tile's halo origin (0, the origin itself, for chunks outside the
-    // ghosted box, which only the stencils of points outside the patch read)
+    // LDS-DMA loads of the halo: chunk j = r NT + tid of the core and wing
+    // rows, its offset from the tile's halo origin and whether a single-axis
+    // field (ndx) or one with second derivatives (ndb) reads it; chunks
+    // outside the ghosted box are read by no stencil of a point of the patch.
+    // Fields with second derivatives load every slot, the ones they do not
+    // read from the tile's first point (one line more; masking those lanes
+    // off instead costs more in branches: 369 against 366 us at 96^3)
     int doff[DMA ? L::NI : 1];
+    bool ndx[DMA ? L::NI : 1];
     if constexpr (DMA) {
 #pragma unroll
         for (int r = 0; r < L::NI; ++r) {
-            const int j = r * NT + tid, ac = j + L::C0, row = ac / L::CPR, cc = ac - row * L::CPR;
-            const int hz = row / HY, hy = row - hz * HY;
-            const bool ok = j < L::NCH && tile.o[0] + 2 * cc < P.n[0] + 2 * G &&
-                            tile.o[1] + hy < P.n[1] + 2 * G && hz < hzmax;
-            doff[r] = ok ? hz * P.pitch_z + hy * P.pitch_y + 2 * cc : 0;
+            const int j = r * NT + tid, rr = j / 4, cc = j % 4;
+            const bool core = rr < L::NCROW;
+            const int row = core ? rr + L::CROW0 : rr - L::NCROW + L::WROW0;
+            const int ho = row / L::HIN, hi = row - ho * L::HIN;
+            const int hy = L::YIN ? hi : ho, hz = L::YIN ? ho : hi;
+            const int hx = core ? G + 2 * cc : (cc < 2 ? G + TX + 2 * cc : G - 4 + 2 * (cc - 2));
+            // distance of the row from the tile's rows along y and z
+            const int dy = hy < G ? G - hy : (hy >= G + TY ? hy - (G + TY) + 1 : 0);
+            const int dz = hz < G ? G - hz : (hz >= G + TZ ? hz - (G + TZ) + 1 : 0);
+            // a chunk may start at the last point of a box row that fills its
+            // pitch: its second double is then the next row's first, so
+            // ghost rows (whose last columns no stencil reads) leave it out
+            const int gy = tile.o[1] + hy, gz = tile.o[2] + hz;
+            const bool inner = gy >= G && gy < P.n[1] + G && gz >= G && gz < P.n[2] + G;
+            const bool in = j < L::NCH && tile.o[0] + hx < P.n[0] + 2 * G - (inner ? 0 : 1) &&
+                            gy < P.n[1] + 2 * G && gz < P.n[2] + 2 * G;
+            const bool x2 = cc == 0 || cc == 3;  // the wing chunk within reach 2 of the tile's columns
+            const bool cross = dy == 0 || dz == 0;
+            ndx[r] = in && (core ? cross : dy == 0 && dz == 0);
+            const bool ndb = in && (core ? cross || (dy <= 2 && dz <= 2)
+                                     : cross && ((dy == 0 && dz == 0) || (x2 && dy <= 2 && dz <= 2)));
+            doff[r] = ndb ? hz * P.pitch_z + hy * P.pitch_y + hx : G * P.pitch_z + G * P.pitch_y + G;
         }
     }
-    auto dma = [&](int f, double* dst) __attribute__((always_inline)) {
+    auto dma = [&](auto fc, double* dst) __attribute__((always_inline)) {
+        constexpr int f = decltype(fc)::value;
         const double* src = a.Us + hbase + (int64_t)f * fs;
         const int wbase = tid & ~63;  // first chunk of this wave's window of 64
 #pragma unroll
         for (int r = 0; r < L::NI; ++r)
-            if ((r + 1) * NT <= L::NCH || r * NT + tid < L::NCH)
+            if (single_axis(f) ? ndx[r] : (r + 1) * NT <= L::NCH || r * NT + tid < L::NCH)
                 __builtin_amdgcn_global_load_lds((const void*)(src + doff[r]), (lds_void*)(dst + 2 * (r * NT + wbase)),
                                                  16, 0, 0);
     };
@@ -363,19 +411,25 @@ __device__ __forceinline__ void ccz4_tile(const StageArgs& a, const CczConst& C,
     double db[3][3], gddb[3], gdiv[3];  // d_k beta^i, gt^jk d_j d_k beta^i, d_i (d_k beta^k)
     double rG[3];                       // Ghat^i terms with d Khat and d Theta
     double alp, A[6], Au[6], Kh, Th, Bv[3];  // point values taken from LDS, At^{ij}
-    const int S[3] = {1, PX, PX * HY};
-    // this point in the halo buffer
-    const int ctr = ((tz + G) * HY + ty + G) * PX + tx + G - (DMA ? 2 * L::C0 : 0);
+    // this point in the halo buffer, its row strides, and the offsets of its
+    // x neighbours (LDS-DMA: in the core row or in the wings)
+    constexpr int SY = DMA ? (L::YIN ? TX : TX * L::HIN) : PX, SZ = DMA ? (L::YIN ? TX * L::HIN : TX) : PX * HY;
+    const int ctr = DMA ? TX * ((rout + G) * L::HIN + rin + G - L::CROW0) + tx : ((tz + G) * HY + ty + G) * PX + tx + G;
+    int xoff[7];
+#pragma unroll
+    for (int m = -3; m <= 3; ++m)
+        xoff[m + 3] = !DMA || (tx + m >= 0 && tx + m < TX)
+                          ? m
+                          : TX * (L::NCROW - L::WROW0 + L::CROW0) + ((tx + m) & (TX - 1)) - tx;
+    auto ax = [&](int m) __attribute__((always_inline)) { return DMA ? xoff[m + 3] : m; };
+    auto ay = [&](int m) __attribute__((always_inline)) { return m * SY; };
+    auto az = [&](int m) __attribute__((always_inline)) { return m * SZ; };
 
     // halo buffer of pass q
-    constexpr int NBUF = L::NBUF;
-    auto hbuf = [&](int q) __attribute__((always_inline)) {
-        return q % NBUF == 0 ? buf : (q % NBUF == 1 ? buf2 : buf3);
-    };
+    auto hbuf = [&](int q) __attribute__((always_inline)) { return DMA && q % 2 ? buf2 : buf; };
     if constexpr (DMA) {
-#pragma unroll
-        for (int q = 0; q + 1 < NBUF; ++q) dma(ORDER[q], hbuf(q));
-        __builtin_amdgcn_s_waitcnt(vm_wait(NBUF == 3 ? L::NIW : 0));
+        dma(std::integral_constant<int, ORDER[0]>{}, buf);
+        __builtin_amdgcn_s_waitcnt(VM_WAIT);
     } else {
         gload(ORDER[0]);
         lstore();
@@ -387,7 +441,7 @@ __device__ __forceinline__ void ccz4_tile(const StageArgs& a, const CczConst& C,
         constexpr int q = decltype(qc)::value;
         constexpr int f = ORDER[q];
         if constexpr (DMA) {
-            if constexpr (q + NBUF - 1 < NF) dma(ORDER[q + NBUF - 1], hbuf(q + NBUF - 1));
+            if constexpr (q + 1 < NF) dma(std::integral_constant<int, ORDER[q + 1]>{}, hbuf(q + 1));
         } else if constexpr (q + 1 < NF) {
             if constexpr (single_axis(ORDER[q + 1]))
                 gload_x(ORDER[q + 1]);
@@ -399,24 +453,28 @@ __device__ __forceinline__ void ccz4_tile(const StageArgs& a, const CczConst& C,
             // advection beta^k d_k and KO dissipation of every field; first
             // and pure second derivatives from the same combinations
             constexpr bool second = (f >= GT && f < GT + 6) || f == CHI || f == ALP || (f >= BETA && f < BETA + 3);
-            double adv = 0.0, ko = 0.0, d1v[3], d2v[3];
+            double ak = 0.0, d1v[3], d2v[3];
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
-                const Axis x = axis(t, S[k]);
-                ko += (x.e3 - 6.0 * x.e2) + 15.0 * x.e1;
+                const Axis x = k == 0 ? axis(t, ax) : (k == 1 ? axis(t, ay) : axis(t, az));
+                const double ko = (x.e3 - 6.0 * x.e2) + 15.0 * x.e1;
                 d1v[k] = 8.0 * x.o1 - x.o2;
+                // explicit fma, so that every tile shape and build rounds alike
                 if (UPWIND)
-                    adv += be[k] * ((0.5 * x.o3 - 3.0 * x.o2) + 10.5 * x.o1) +
-                           fabs(be[k]) * ((0.5 * x.e3 - 3.0 * x.e2) + 7.5 * x.e1);
+                    ak = fma(be[k], fma(10.5, x.o1, fma(0.5, x.o3, -3.0 * x.o2)),
+                             fma(fma(0.5, fabs(be[k]), C.koa), ko, ak));
                 else
-                    adv += be[k] * d1v[k];
+                    ak = fma(be[k], d1v[k], fma(C.koa, ko, ak));
                 if constexpr (second) d2v[k] = 16.0 * x.e1 - x.e2;
             }
-            akx[f][tid] = C.i12h * adv + C.ko * ko;
+            akx[f][tid] = C.i12h * ak;
 
             auto d1 = [&](int k) __attribute__((always_inline)) { return C.i12h * d1v[k]; };
             auto dd = [&](int k, int l) __attribute__((always_inline)) {
-                return k == l ? C.i12h2 * d2v[k] : C.i144h2 * fmix(t, S[k], S[l]);
+                if (k == l) return C.i12h2 * d2v[k];
+                // in either order: axis a first, then b > a
+                const int a = k < l ? k : l, b = k < l ? l : k;
+                return C.i144h2 * (a == 0 ? lds_mix(t, ax, b == 1 ? SY : SZ) : lds_mix(t, ay, SZ));
             };
             // gt^{kl} d_k d_l of the field in LDS
             auto trdd = [&]() __attribute__((always_inline)) {
@@ -614,10 +672,9 @@ __device__ __forceinline__ void ccz4_tile(const StageArgs& a, const CczConst& C,
             }
         }
         if constexpr (DMA) {
-            // the next field's halo has arrived (the loads of the field after
-            // it may still be in flight), and every wave is done with this
-            // buffer before the load issued in the pass NBUF - 1 ahead refills it
-            if constexpr (q + 1 < NF) __builtin_amdgcn_s_waitcnt(vm_wait(NBUF == 3 && q + 2 < NF ? L::NIW : 0));
+            // the next field's halo has arrived, and every wave is done with
+            // this buffer before the next pass refills it
+            if constexpr (q + 1 < NF) __builtin_amdgcn_s_waitcnt(VM_WAIT);
             lds_barrier();
         } else {
             __syncthreads();
@@ -711,7 +768,7 @@ __device__ __forceinline__ void ccz4_tile(const StageArgs& a, const CczConst& C,
             const int m = SI(i, j);
             double r = 0.0;
 #pragma unroll
-            for (int k = 0; k < 3; ++k) r += g[SI(i, k)] * db[j][k] + g[SI(k, j)] * db[i][k];
+            for (int k = 0; k < 3; ++k) r = fma(g[SI(k, j)], db[i][k], fma(g[SI(i, k)], db[j][k], r));
             out(GT + m, r - (2.0 / 3.0) * g[m] * divb - 2.0 * alp * (A[m] - (1.0 / 3.0) * g[m] * trA) -
                             (C.kc / 3.0) * alp * g[m] * lndet);
         }
@@ -729,7 +786,7 @@ __device__ __forceinline__ void ccz4_tile(const StageArgs& a, const CczConst& C,
                 double r = 0.0, aa = 0.0;
 #pragma unroll
                 for (int k = 0; k < 3; ++k) {
-                    r += A[SI(i, k)] * db[j][k] + A[SI(k, j)] * db[i][k];
+                    r = fma(A[SI(k, j)], db[i][k], fma(A[SI(i, k)], db[j][k], r));
                     aa += A[SI(i, k)] * Am[k][j];
                 }
                 out(AT + m, r - (2.0 / 3.0) * A[m] * divb - (C.kc / 3.0) * alp * g[m] * trA +
@@ -763,34 +820,9 @@ __global__ __launch_bounds__(TX * TY * TZ, MOL_CCZ4_WAVES) void ccz4_stage_kerne
 {
     using L = CczLds<TX, TY, TZ>;
     __shared__ double buf[L::LB];
-    __shared__ double buf2[L::NBUF >= 2 ? L::LB : 1];
-    __shared__ double buf3[L::NBUF >= 3 ? L::LB : 1];
+    __shared__ double buf2[L::DMA ? L::LB : 1];
     __shared__ double akx[NF][L::NT];
-    ccz4_tile<TX, TY, TZ, UPWIND>(a, C, xcd_tile(blockIdx.x, gridDim.x), buf, buf2, buf3, akx);
-}
-
-// Persistent form: a grid of at most as many workgroups as are resident at
-// once; the workgroups of XCD x (x = blockIdx mod 8) take the tiles of that
-// XCD's contiguous range of the tile list in turn, so that concurrently
-// running tiles of an XCD stay spatial neighbours, and every workgroup exits
-// after its last tile.
-template <int TX, int TY, int TZ, bool UPWIND>
-__global__ __launch_bounds__(TX * TY * TZ, MOL_CCZ4_WAVES) void ccz4_stage_persistent_kernel(StageArgs a, CczConst C)
-{
-    using L = CczLds<TX, TY, TZ>;
-    __shared__ double buf[L::LB];
-    __shared__ double buf2[L::NBUF >= 2 ? L::LB : 1];
-    __shared__ double buf3[L::NBUF >= 3 ? L::LB : 1];
-    __shared__ double akx[NF][L::NT];
-    constexpr int NXCD = 8;
-    const int n = a.ntiles, x = blockIdx.x % NXCD, slot = blockIdx.x / NXCD;
-    const int per = n / NXCD, rem = n % NXCD;
-    const int lo = x * per + (x < rem ? x : rem), hi = lo + per + (x < rem ? 1 : 0);
-    const int nwg = ((int)gridDim.x - x + NXCD - 1) / NXCD;  // workgroups of this XCD
-    for (int t = lo + slot; t < hi; t += nwg) {
-        ccz4_tile<TX, TY, TZ, UPWIND>(a, C, t, buf, buf2, buf3, akx);
-        __syncthreads();  // the next tile overwrites buf and akx
-    }
+    ccz4_tile<TX, TY, TZ, UPWIND>(a, C, xcd_tile(blockIdx.x, gridDim.x), buf, buf2, akx);
 }
 
 }  // namespace
@@ -819,7 +851,7 @@ hipError_t launch_stage_ccz4(const SysParams& sp, const StageArgs& a, const int 
     C.i12h = 1.0 / (12.0 * sp.h);
     C.i12h2 = 1.0 / (12.0 * sp.h * sp.h);
     C.i144h2 = 1.0 / (144.0 * sp.h * sp.h);
-    C.ko = sp.sigma / (64.0 * sp.h);
+    C.koa = sp.sigma * (12.0 / 64.0);
     C.kz = sp.kappa_z;
     C.kc = sp.kappa_c;
     C.f0 = sp.bm_f0;
@@ -828,28 +860,10 @@ hipError_t launch_stage_ccz4(const SysParams& sp, const StageArgs& a, const int 
     C.eta = sp.gd_eta;
     if (!dflt) return t888 ? launch_ccz4_tile<8, 8, 8>(sp, a, C, s) : launch_ccz4_tile<8, 4, 8>(sp, a, C, s);
     dim3 blk(MOL_CCZ4_TX, MOL_CCZ4_TY, MOL_CCZ4_TZ);
-#if MOL_CCZ4_PERSISTENT
-    // as many workgroups as are resident at once: MOL_CCZ4_WAVES waves per
-    // SIMD, four SIMDs per compute unit
-    static int cus[64] = {};
-    int dev = 0;
-    hipError_t e = hipGetDevice(&dev);
-    if (e != hipSuccess) return e;
-    if (dev < 0 || dev >= 64) return hipErrorInvalidDevice;
-    if (!cus[dev] && (e = hipDeviceGetAttribute(&cus[dev], hipDeviceAttributeMultiprocessorCount, dev)) != hipSuccess)
-        return e;
-    constexpr int wg_per_cu = MOL_CCZ4_WAVES * 4 / (MOL_CCZ4_TX * MOL_CCZ4_TY * MOL_CCZ4_TZ / 64);
-    const int grid = std::min(a.ntiles, cus[dev] * std::max(wg_per_cu, 1));
-    if (sp.upwind)
-        ccz4_stage_persistent_kernel<MOL_CCZ4_TX, MOL_CCZ4_TY, MOL_CCZ4_TZ, true><<<grid, blk, 0, s>>>(a, C);
-    else
-        ccz4_stage_persistent_kernel<MOL_CCZ4_TX, MOL_CCZ4_TY, MOL_CCZ4_TZ, false><<<grid, blk, 0, s>>>(a, C);
-#else
     if (sp.upwind)
         ccz4_stage_kernel<MOL_CCZ4_TX, MOL_CCZ4_TY, MOL_CCZ4_TZ, true><<<a.ntiles, blk, 0, s>>>(a, C);
     else
         ccz4_stage_kernel<MOL_CCZ4_TX, MOL_CCZ4_TY, MOL_CCZ4_TZ, false><<<a.ntiles, blk, 0, s>>>(a, C);
-#endif
     return hipGetLastError();
 }
 

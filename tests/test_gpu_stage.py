@@ -391,3 +391,26 @@ def test_level_layout_row_alignment(n):
                 row = off + f * fs + ((k + 3) * (n[1] + 6) + j + 3) * px + 3
                 assert row % align == 0, (f, j, k)
     assert ps.alloc(0).data_ptr() % 256 == 0
+
+
+@pytest.mark.parametrize("tdim", [(8, 8, 4), (8, 8, 8), (8, 4, 8)])
+@pytest.mark.parametrize("n", [(26, 10, 7), (8, 8, 4), (34, 17, 3), (10, 9, 12)])
+def test_ccz4_halo_chunks_at_patch_edges(n, tdim):
+    """The stage kernel's halo loads at the edges of a patch: rows whose
+    ghosted box fills its pitch (26 and 34 points: the last chunk of a row is
+    followed by the next row), a patch of whole tiles, and ragged tails along
+    every axis, for every tile shape, against the oracle (one RK4 step)."""
+    torch = _torch()
+    print("ccz4 halo chunks", n, tdim, flush=True)
+    st0, dx = _ccz4_state(n, "strong")
+    U0 = synth.embed(st0)
+    ps = M.Patchset(M.single_patch(n, (0, 0, 0), dx), M.System(M.MOL_CCZ4))
+    ps.set_tiling(0, tdim)
+    st = ps.alloc_states()
+    st[0]["U"].copy_(torch.from_numpy(ps.pack(0, [U0])))
+    ps.advance(st, 0.25 * dx)
+    torch.cuda.synchronize()
+    got = ps.unpack(0, st[0]["U"])[0]
+    ref = _oracle_steps(O.CCZ4, O.RK4, U0, dx, 0.25 * dx, 1, O.params())
+    e = parity_err(got[:, 3:-3, 3:-3, 3:-3], ref[:, 3:-3, 3:-3, 3:-3])
+    assert np.all(e <= TOL), e
