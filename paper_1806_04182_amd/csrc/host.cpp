@@ -215,10 +215,11 @@ struct mol_patchset {
         std::vector<int64_t> fill_by_patch;
         DevArr<GhostSource> fill_src;
         DevArr<GhostImage> fill_img;
-        // coarse-fine ghost points (this level is the fine one) grouped by
-        // parent cell, by dst patch
-        DevArr<ProlongCell> pcell;
-        std::vector<int64_t> pcell_by_patch;
+        // coarse-fine ghost points (this level is the fine one) in bricks of
+        // parent cells, by dst patch, and the bricks' row masks
+        DevArr<ProlongBrick> pbrick;
+        DevArr<uint32_t> prow;
+        std::vector<int64_t> pbrick_by_patch;
         std::vector<double> lagw;  // Lagrange weights [R][6]
         // parent points read by the prolongation stencils of this level: the
         // position in a parent patch's ghosted box (dst) and the interior
@@ -252,7 +253,8 @@ struct mol_patchset {
             l.fill.release();
             l.fill_src.release();
             l.fill_img.release();
-            l.pcell.release();
+            l.pbrick.release();
+            l.prow.release();
             l.band.release();
             l.rst.release();
             l.tiles.dev.release();
@@ -273,12 +275,14 @@ struct mol_regrid {
     mol_patchset* pn = nullptr;
     const mol_patchset* po = nullptr;
     DevArr<GhostCopy> copy[MOL_MAX_LEVELS];   // new <- old at the same level
-    DevArr<ProlongCell> cells[MOL_MAX_LEVELS];  // new points interpolated from the new parent
+    DevArr<ProlongBrick> bricks[MOL_MAX_LEVELS];  // new points interpolated from the new parent
+    DevArr<uint32_t> rows[MOL_MAX_LEVELS];
     ~mol_regrid()
     {
         for (int l = 0; l < MOL_MAX_LEVELS; ++l) {
             copy[l].release();
-            cells[l].release();
+            bricks[l].release();
+            rows[l].release();
         }
     }
 };
@@ -355,6 +359,100 @@ struct ProlongPt {
 };
 
 int floor_div(int a, int b) { return a >= 0 ? a / b : -((-a + b - 1) / b); }
+
+// Parent cells holding the interpolated points of one fine patch: cell
+// coordinates floor(g / R) (unwrapped), the parent patch that owns the cell's
+// node i0 and i0's wrapped position, and the present points m.
+struct FineCells {
+    struct Cell {
+        int key[3], q0, cw[3];
+        uint64_t mask;
+    };
+    std::vector<Cell> cells;
+    std::map<std::array<int, 3>, size_t> index;
+    void add(const int g[3], const int m[3], int R, int q0, const int cw[3])
+    {
+        const std::array<int, 3> key = {floor_div(g[0], R), floor_div(g[1], R), floor_div(g[2], R)};
+        auto it = index.find(key);
+        if (it == index.end()) {
+            it = index.emplace(key, cells.size()).first;
+            cells.push_back(Cell{{key[0], key[1], key[2]}, q0, {cw[0], cw[1], cw[2]}, 0});
+        }
+        cells[it->second].mask |= uint64_t(1) << ((m[2] * R + m[1]) * R + m[0]);
+    }
+    // append the cells' bricks: cells of one parent patch and one wrap offset
+    // in blocks aligned at the lowest cell, each cut to the bounding box of
+    // its cells.  Cells in the two outermost layers along z take shape 0, else
+    // along y shape 1, else along x shape 2 (their slabs), the others shape 0.
+    void bricks(const PatchDev& pd, const Level& par, int R, std::vector<ProlongBrick>& out,
+                std::vector<uint32_t>& rows) const
+    {
+        if (cells.empty()) return;
+        int lo[3], hi[3];
+        for (int d = 0; d < 3; ++d) lo[d] = hi[d] = cells[0].key[d];
+        for (const Cell& c : cells)
+            for (int d = 0; d < 3; ++d) {
+                lo[d] = std::min(lo[d], c.key[d]);
+                hi[d] = std::max(hi[d], c.key[d]);
+            }
+        std::map<std::array<int, 8>, std::vector<size_t>> blocks;
+        for (size_t t = 0; t < cells.size(); ++t) {
+            const Cell& c = cells[t];
+            auto face = [&](int d) { return c.key[d] < lo[d] + 2 ? 1 : (c.key[d] > hi[d] - 2 ? 2 : 0); };
+            // axis of the slab (-1: none) and its side
+            const int ax = face(2) ? 2 : (face(1) ? 1 : (face(0) ? 0 : -1));
+            const int shape = ax == 1 ? 1 : (ax == 0 ? 2 : 0);
+            std::array<int, 8> id;
+            id[0] = c.q0;
+            for (int d = 0; d < 3; ++d) {
+                id[1 + d] = c.cw[d] - c.key[d];
+                id[4 + d] = (c.key[2 - d] - lo[2 - d]) / brick_dim(R, shape, 2 - d);
+            }
+            // the two layers of a high face share a block whatever its alignment
+            if (ax >= 0) id[4 + (2 - ax)] = face(ax);
+            id[7] = 4 * ax;
+            blocks[id].push_back(t);
+        }
+        for (const auto& bl : blocks) {
+            int k0[3], k1[3];
+            for (int d = 0; d < 3; ++d) k0[d] = k1[d] = cells[bl.second[0]].key[d];
+            for (size_t t : bl.second)
+                for (int d = 0; d < 3; ++d) {
+                    k0[d] = std::min(k0[d], cells[t].key[d]);
+                    k1[d] = std::max(k1[d], cells[t].key[d]);
+                }
+            const PatchDev& qd = par.pd[bl.first[0]];
+            ProlongBrick e{};
+            int c0[3], d0[3];
+            for (int d = 0; d < 3; ++d) {
+                e.n[d] = k1[d] - k0[d] + 1;
+                c0[d] = k0[d] + bl.first[1 + d] - qd.lo[d] + G - 2;
+                d0[d] = R * k0[d] - pd.lo[d] + G;
+            }
+            e.dbase = pd.off + local_index(pd, d0[0], d0[1], d0[2]);
+            e.cbase = qd.off + local_index(qd, c0[0], c0[1], c0[2]);
+            e.dfs = pd.fs;
+            e.cfs = qd.fs;
+            e.dpy = pd.pitch_y;
+            e.dpz = pd.pitch_z;
+            e.cpy = qd.pitch_y;
+            e.cpz = qd.pitch_z;
+            e.rows = (int32_t)rows.size();
+            const int fy = e.n[1] * R;
+            rows.resize(rows.size() + (size_t)fy * e.n[2] * R, 0u);
+            for (size_t t : bl.second) {
+                const Cell& c = cells[t];
+                for (int mz = 0; mz < R; ++mz)
+                    for (int my = 0; my < R; ++my)
+                        for (int mx = 0; mx < R; ++mx)
+                            if (c.mask >> ((mz * R + my) * R + mx) & 1)
+                                rows[e.rows + ((c.key[2] - k0[2]) * R + mz) * fy + (c.key[1] - k0[1]) * R + my] |=
+                                    1u << ((c.key[0] - k0[0]) * R + mx);
+            }
+            out.push_back(e);
+        }
+    }
+};
 
 // tiles of td[0] x td[1] x td[2] points over every patch (grown by margin),
 // each patch's tiles contiguous; patches in the given order (0: as listed,
@@ -444,8 +542,9 @@ void reuse_level(mol_patchset* ps, const mol_patchset* prev, int l)
     lev.fill_by_patch = o.fill_by_patch;
     lev.fill_src.adopt(o.fill_src, A);
     lev.fill_img.adopt(o.fill_img, A);
-    lev.pcell.adopt(o.pcell, A);
-    lev.pcell_by_patch = o.pcell_by_patch;
+    lev.pbrick.adopt(o.pbrick, A);
+    lev.prow.adopt(o.prow, A);
+    lev.pbrick_by_patch = o.pbrick_by_patch;
     lev.lagw = o.lagw;
     lev.band.adopt(o.band, A);
     lev.band_by_patch = o.band_by_patch;
@@ -563,9 +662,10 @@ int build(mol_patchset* ps, const mol_hierarchy_desc* h, const mol_patchset* pre
         std::vector<RadPt> rad;
         std::vector<ProlongPt> pro;
         std::vector<int64_t> pro_by_patch(lev.pd.size() + 1, 0);
-        std::vector<ProlongCell> cells;
+        std::vector<ProlongBrick> bricks;
+        std::vector<uint32_t> brows;
         lev.fill_by_patch.assign(lev.pd.size() + 1, 0);
-        lev.pcell_by_patch.assign(lev.pd.size() + 1, 0);
+        lev.pbrick_by_patch.assign(lev.pd.size() + 1, 0);
         const Level* par = l > 0 ? &ps->L[l - 1] : nullptr;
         std::vector<std::vector<int>> pcand;
         std::vector<int> allpar;
@@ -577,17 +677,9 @@ int build(mol_patchset* ps, const mol_hierarchy_desc* h, const mol_patchset* pre
         for (size_t p = 0; p < lev.pd.size(); ++p) {
             lev.fill_by_patch[p] = (int64_t)fill.size();
             pro_by_patch[p] = (int64_t)pro.size();
-            lev.pcell_by_patch[p] = (int64_t)cells.size();
+            lev.pbrick_by_patch[p] = (int64_t)bricks.size();
             const PatchDev& pd = lev.pd[p];
-            // parent cells of this patch's coarse-fine ghost points: cell
-            // coordinates floor(g / R), owner patch and owned position of i0
-            struct CellTmp {
-                int key[3], q0, cw[3];
-                uint64_t mask;
-                int frac;
-            };
-            std::vector<CellTmp> ct;
-            std::map<std::array<int, 3>, size_t> cidx;
+            FineCells fc;
             for (int k = -G; k < pd.n[2] + G; ++k)
                 for (int j = -G; j < pd.n[1] + G; ++j)
                     for (int i = -G; i < pd.n[0] + G; ++i) {
@@ -642,44 +734,16 @@ int build(mol_patchset* ps, const mol_hierarchy_desc* h, const mol_patchset* pre
                         e.cpz = qd.pitch_z;
                         for (int d = 0; d < 3; ++d) e.m[d] = (int8_t)m[d];
                         pro.push_back(e);
-                        const std::array<int, 3> key = {floor_div(g[0], R), floor_div(g[1], R), floor_div(g[2], R)};
-                        auto it = cidx.find(key);
-                        if (it == cidx.end()) {
-                            it = cidx.emplace(key, ct.size()).first;
-                            ct.push_back(CellTmp{{key[0], key[1], key[2]}, q0, {cw[0], cw[1], cw[2]}, 0, 0});
-                        }
-                        CellTmp& c = ct[it->second];
-                        c.mask |= uint64_t(1) << ((m[2] * R + m[1]) * R + m[0]);
-                        for (int d = 0; d < 3; ++d)
-                            if (m[d]) c.frac |= 1 << d;
+                        fc.add(g, m, R, q0, cw);
                     }
-            // cells ordered by their fractional axes (uniform work within a wave)
-            std::stable_sort(ct.begin(), ct.end(), [](const CellTmp& a, const CellTmp& b) { return a.frac < b.frac; });
-            for (const CellTmp& c : ct) {
-                const PatchDev& qd = par->pd[c.q0];
-                int c0[3];
-                for (int d = 0; d < 3; ++d) c0[d] = c.cw[d] - qd.lo[d] + G - ((c.frac >> d & 1) ? 2 : 0);
-                ProlongCell e{};
-                e.dbase = pd.off + local_index(pd, R * c.key[0] - pd.lo[0] + G, R * c.key[1] - pd.lo[1] + G,
-                                               R * c.key[2] - pd.lo[2] + G);
-                e.cbase = qd.off + local_index(qd, c0[0], c0[1], c0[2]);
-                e.dfs = pd.fs;
-                e.cfs = qd.fs;
-                e.dpy = pd.pitch_y;
-                e.dpz = pd.pitch_z;
-                e.cpy = qd.pitch_y;
-                e.cpz = qd.pitch_z;
-                e.mask = c.mask;
-                e.frac = c.frac;
-                cells.push_back(e);
-            }
+            if (par) fc.bricks(pd, *par, R, bricks, brows);
         }
         lev.fill_by_patch[lev.pd.size()] = (int64_t)fill.size();
         pro_by_patch[lev.pd.size()] = (int64_t)pro.size();
-        lev.pcell_by_patch[lev.pd.size()] = (int64_t)cells.size();
+        lev.pbrick_by_patch[lev.pd.size()] = (int64_t)bricks.size();
         if ((rc = lev.fill.upload(fill, &ps->arena))) return rc;
         if (l == 0 && ps->open && (rc = ps->rad_pts.upload(rad, &ps->arena))) return rc;
-        if ((rc = lev.pcell.upload(cells, &ps->arena))) return rc;
+        if ((rc = lev.pbrick.upload(bricks, &ps->arena)) || (rc = lev.prow.upload(brows, &ps->arena))) return rc;
         if (par) {
             // every parent point that some stencil reads, once, grouped by the
             // fine patch that first needs it (so per-patch launches cover it)
@@ -1021,9 +1085,10 @@ int prolong_impl(mol_patchset* ps, int fl, int r, int stage, const double* Unc,
         if (e != hipSuccess) return hip_fail(e, "BOR band launch");
     }
     for (int p = 0; p < nl; ++p) {
-        const int64_t b0 = plain ? lev.pcell_by_patch[p] : 0;
-        const int64_t bn = plain ? lev.pcell_by_patch[p + 1] - b0 : lev.pcell.n;
-        hipError_t e = launch_prolong(lev.pcell.p + b0, bn, nf, lev.ratio, lev.lagw.data(), ps->tband, Uf, st);
+        const int64_t b0 = plain ? lev.pbrick_by_patch[p] : 0;
+        const int64_t bn = plain ? lev.pbrick_by_patch[p + 1] - b0 : lev.pbrick.n;
+        hipError_t e = launch_prolong(lev.pbrick.p + b0, bn, lev.prow.p, nf, lev.ratio, lev.lagw.data(), ps->tband, Uf,
+                                      st);
         if (e != hipSuccess) return hip_fail(e, "prolong launch");
     }
     return MOL_OK;
@@ -1845,16 +1910,11 @@ int mol_regrid_create(mol_patchset* pn, const mol_patchset* po, mol_regrid** out
         for (size_t q = 0; q < old.boxes.size(); ++q) allold.push_back((int)q);
         for (size_t q = 0; q < par.boxes.size(); ++q) allpar.push_back((int)q);
         std::vector<GhostCopy> copy;
-        std::vector<ProlongCell> cells;
+        std::vector<ProlongBrick> bricks;
+        std::vector<uint32_t> rows;
         for (size_t p = 0; p < lev.pd.size(); ++p) {
             const PatchDev& pd = lev.pd[p];
-            struct CellTmp {
-                int key[3], q0, cw[3];
-                uint64_t mask;
-                int frac;
-            };
-            std::vector<CellTmp> ct;
-            std::map<std::array<int, 3>, size_t> cidx;
+            FineCells fc;
             for (int k = 0; k < pd.n[2]; ++k)
                 for (int j = 0; j < pd.n[1]; ++j)
                     for (int i = 0; i < pd.n[0]; ++i) {
@@ -1889,39 +1949,12 @@ int mol_regrid_create(mol_patchset* pn, const mol_patchset* po, mol_regrid** out
                                                     "parent level", l);
                                     }
                                 }
-                        const std::array<int, 3> key = {floor_div(g[0], R), floor_div(g[1], R), floor_div(g[2], R)};
-                        auto it = cidx.find(key);
-                        if (it == cidx.end()) {
-                            it = cidx.emplace(key, ct.size()).first;
-                            ct.push_back(CellTmp{{key[0], key[1], key[2]}, q0, {cw[0], cw[1], cw[2]}, 0, 0});
-                        }
-                        CellTmp& c = ct[it->second];
-                        c.mask |= uint64_t(1) << ((m[2] * R + m[1]) * R + m[0]);
-                        for (int d = 0; d < 3; ++d)
-                            if (m[d]) c.frac |= 1 << d;
+                        fc.add(g, m, R, q0, cw);
                     }
-            std::stable_sort(ct.begin(), ct.end(), [](const CellTmp& a, const CellTmp& b) { return a.frac < b.frac; });
-            for (const CellTmp& c : ct) {
-                const PatchDev& qd = par.pd[c.q0];
-                int c0[3];
-                for (int d = 0; d < 3; ++d) c0[d] = c.cw[d] - qd.lo[d] + G - ((c.frac >> d & 1) ? 2 : 0);
-                ProlongCell e{};
-                e.dbase = pd.off + local_index(pd, R * c.key[0] - pd.lo[0] + G, R * c.key[1] - pd.lo[1] + G,
-                                               R * c.key[2] - pd.lo[2] + G);
-                e.cbase = qd.off + local_index(qd, c0[0], c0[1], c0[2]);
-                e.dfs = pd.fs;
-                e.cfs = qd.fs;
-                e.dpy = pd.pitch_y;
-                e.dpz = pd.pitch_z;
-                e.cpy = qd.pitch_y;
-                e.cpz = qd.pitch_z;
-                e.mask = c.mask;
-                e.frac = c.frac;
-                cells.push_back(e);
-            }
+            fc.bricks(pd, par, R, bricks, rows);
         }
         int rc;
-        if ((rc = r->copy[l].upload(copy)) || (rc = r->cells[l].upload(cells))) {
+        if ((rc = r->copy[l].upload(copy)) || (rc = r->bricks[l].upload(bricks)) || (rc = r->rows[l].upload(rows))) {
             delete r;
             return rc;
         }
@@ -1945,8 +1978,8 @@ int mol_regrid_apply(mol_regrid* r, const double* const* U_old, double* const* U
         if (rc) return rc;
         if ((e = launch_copy2(r->copy[l].p, r->copy[l].n, nf, U_old[l], U_new[l], s)) != hipSuccess)
             return hip_fail(e, "regrid copy launch");
-        if ((e = launch_prolong(r->cells[l].p, r->cells[l].n, nf, pn->L[l].ratio, pn->L[l].lagw.data(), U_new[l - 1],
-                                U_new[l], s)) != hipSuccess)
+        if ((e = launch_prolong(r->bricks[l].p, r->bricks[l].n, r->rows[l].p, nf, pn->L[l].ratio,
+                                pn->L[l].lagw.data(), U_new[l - 1], U_new[l], s)) != hipSuccess)
             return hip_fail(e, "regrid interpolation launch");
     }
     return MOL_OK;

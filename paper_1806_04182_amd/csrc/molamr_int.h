@@ -80,23 +80,50 @@ struct GhostImage {
     int64_t dfs;
 };
 
-// Coarse-fine ghost points of one fine patch grouped by parent cell: the
-// fine points R i0 + m (m in [0, R)^3) of parent cell i0.  Bit
-// (mz R + my) R + mx of mask marks the points present.  Axis d is fractional
-// (bit d of frac) when some present point has m_d != 0; the stencil then
-// spans parent nodes i0-2 .. i0+3 on that axis, otherwise only i0; cbase is
-// the stencil corner.  dbase is the fine-level index of the point m = 0,
-// which may lie outside the fine patch's ghosted box.
-struct ProlongCell {
+// Coarse-fine ghost points (or new points of a regrid) of one fine patch in
+// bricks of parent cells: n[0] x n[1] x n[2] cells of one parent patch's box
+// (at most brick_dim), holding the fine points R i0 + m (m in [0, R)^3) of
+// each cell i0.  cbase is the parent node i0 - (2, 2, 2) of the first cell,
+// dbase the fine point m = 0 of the first cell (which may lie outside the
+// fine patch's ghosted box).  rows: start of the brick's row masks, one word
+// per fine row (z slow, then y: n[2] R x n[1] R rows), bit x set when fine
+// point x of the row is present.
+struct ProlongBrick {
     int64_t dbase;
     int64_t cbase;
     int64_t dfs, cfs;  // field strides (fine, parent)
     int32_t dpy, dpz;  // fine pitches
     int32_t cpy, cpz;  // parent pitches
-    uint64_t mask;
-    int32_t frac;
-    int32_t pad;
+    int32_t n[3];
+    int32_t rows;
 };
+// Brick shapes (cells per axis) at ratio R: shape 0 for cells in general and
+// for slabs two cells thick along z, 1 and 2 for slabs two thick along y and
+// x (the ghost shell of a patch is six such slabs), so that a brick holds
+// about as many cells whatever its orientation.  A fine row fits 32 bits.
+constexpr int brick_dim(int R, int shape, int d)
+{
+    constexpr int B[3][3][3] = {{{8, 8, 4}, {8, 2, 8}, {2, 8, 8}},
+                                {{8, 4, 4}, {8, 2, 6}, {2, 8, 8}},
+                                {{4, 4, 4}, {4, 2, 6}, {2, 6, 6}}};
+    return B[R - 2][shape][d];
+}
+// Values of the largest brick's interpolation stages: nodes (0), cells and
+// rows of nodes after x (1), fine x and cells after y (2), fine x and y and
+// cells after z (3)
+constexpr int brick_items(int R, int stage)
+{
+    int m = 0;
+    for (int s = 0; s < 3; ++s) {
+        const int x = brick_dim(R, s, 0), y = brick_dim(R, s, 1), z = brick_dim(R, s, 2);
+        const int v = stage == 0   ? (x + 5) * (y + 5) * (z + 5)
+                      : stage == 1 ? x * (y + 5) * (z + 5)
+                      : stage == 2 ? x * R * y * (z + 5)
+                                   : x * R * y * R * z;
+        m = v > m ? v : m;
+    }
+    return m;
+}
 
 // Injection: fine offset, coarse offset (field 0) and field strides.
 struct RestrictPt {
@@ -179,8 +206,8 @@ hipError_t launch_fill_adjoint(const GhostSource* src, int64_t nsrc, const Ghost
 hipError_t launch_bor_band(const GhostCopy* band, int64_t n, int nf, const double w[4], const double* Un,
                            const double* k0, const double* k1, const double* k2, const double* k3, double* T,
                            hipStream_t s);
-hipError_t launch_prolong(const ProlongCell* e, int64_t n, int nf, int R, const double* lw_host, const double* T,
-                          double* U, hipStream_t s);
+hipError_t launch_prolong(const ProlongBrick* e, int64_t n, const uint32_t* rows, int nf, int R,
+                          const double* lw_host, const double* T, double* U, hipStream_t s);
 hipError_t launch_restrict(const RestrictPt* e, int64_t n, int nf, const double* Uf, double* Uc,
                            hipStream_t s);
 int ccz4_adjoint_slots();

@@ -470,3 +470,50 @@ def test_multi_step_calls_equal_repeated_steps(case):
     for other in results[1:]:
         for a, b in zip(results[0], other):
             assert np.array_equal(a.view(np.uint64), b.view(np.uint64))
+
+
+@pytest.mark.parametrize("split", [False, True])
+@pytest.mark.parametrize("R", [2, 3, 4])
+def test_prolong_bricks_reproduce_quintic_polynomials(R, split):
+    """Interpolation of a polynomial of degree 5 per axis into the ghosts of
+    fine patches whose shells take every brick shape (a thin, an odd and a
+    long patch, two of them adjacent), from one and from several parent
+    patches: the coarse-fine ghosts equal the polynomial times
+    1 + sum_j w_j c_j (k_j = c_j U^n) and every other point is left alone.
+    Tolerance: per axis at most 1.4 times max|p| in the sums of six terms, so
+    1.4^3 * 2^-53 * (18 + 4 roundings) * |value| <= 2, under 2e-14; 5e-14."""
+    torch = _torch()
+    print("prolong bricks", R, split, flush=True)
+    N = 36
+    l0 = [((0, 0, 0), (N - 1,) * 3)] if not split else \
+        [((0, 0, 0), (16, N - 1, N - 1)), ((17, 0, 0), (N - 1, 13, N - 1)), ((17, 14, 0), (N - 1, N - 1, N - 1))]
+    a = 8 * R
+    l1 = [((a + 1, a, a), (a + 1 + 6 * R, a + 4, a + 16 * R + 1)),
+          ((a + 1, a + 5, a), (a + 3 + 10 * R, a + 5 + 5 * R, a + 2)),
+          ((a + 18 * R, a + 12 * R, a + 8 * R), (a + 18 * R, a + 12 * R + 1, a + 8 * R + 6))]
+    ps = M.Patchset(M.Hierarchy((N, N, N), (0, 0, 0), 1.0, [(1, l0), (R, l1)]), M.System(M.MOL_WAVE, sigma=0.0))
+
+    def poly(lo, hi, h):  # |p| <= 1 on [0, N)^3, ghosted box of the patch
+        x = [h * np.arange(lo[d] - 3, hi[d] + 4) / N - 0.5 for d in range(3)]
+        f = [32.0 * x[0] ** 5 - 0.3 * x[0], 16.0 * x[1] ** 4 - 0.2, 1.0 - 24.0 * x[2] ** 5 + x[2]]
+        p = 0.3 * f[2][:, None, None] * f[1][None, :, None] * f[0][None, None, :]
+        return np.stack([p, 0.7 - 0.5 * p])
+
+    Un = torch.from_numpy(ps.pack(0, [poly(lo, hi, 1.0) for lo, hi in l0])).cuda()
+    c = [0.3, -0.2, 0.15, 0.4]
+    k = [cj * Un for cj in c]
+    r, stage = R - 1, 3
+    scale = 1.0 + float(np.dot(M.bor_weights(R, r, stage), c))
+    U = torch.full((ps.layouts[1]["nelems"],), 7.0, dtype=torch.float64, device="cuda")
+    ps.prolong(1, r, stage, Un, k, U)
+    torch.cuda.synchronize()
+    inside = lambda g: any(all(lo[d] <= g[d] <= hi[d] for d in range(3)) for lo, hi in l1)  # noqa: E731
+    for (lo, hi), got in zip(l1, ps.unpack(1, U)):
+        ref = scale * poly(lo, hi, 1.0 / R)
+        for z in range(got.shape[1]):
+            for y in range(got.shape[2]):
+                for x in range(got.shape[3]):
+                    if inside((lo[0] + x - 3, lo[1] + y - 3, lo[2] + z - 3)):
+                        ref[:, z, y, x] = 7.0
+        assert np.max(np.abs(got - ref)) < 5e-14
+
