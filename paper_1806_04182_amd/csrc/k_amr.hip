@@ -17,6 +17,14 @@ int grid_for(int64_t n)
     return (int)(b < 1 ? 1 : (b > 65535 * 8 ? 65535 * 8 : b));
 }
 
+// Launches of one thread per (point, field or group of fields): points along
+// x, fields along y, so that no thread divides 64-bit indices to find its
+// point (the channel's coarse step of 14 fills and 8 band launches: 178 ->
+// 172 us; large launches do not change)
+dim3 grid_for(int64_t n, int nf) { return dim3(grid_for(n), nf, 1); }
+__device__ __forceinline__ int64_t first_point() { return blockIdx.x * (int64_t)BLK + threadIdx.x; }
+__device__ __forceinline__ int64_t next_point() { return (int64_t)gridDim.x * BLK; }
+
 // Copies of nf fields between two points: the loads of up to FC fields are
 // issued together before their stores.
 constexpr int FC = 8;
@@ -35,18 +43,16 @@ __device__ __forceinline__ void copy_fields(const double* __restrict__ src, int6
 }
 
 // same-level / periodic copy: ghost <- interior point of the owning patch.
-// One thread per (ghost point, group of FC fields), the group the slow index,
+// One thread per (ghost point, group of FC fields), the group in the grid's y,
 // so that a launch has ceil(nf / FC) times as many threads, each with one
 // batch of loads in flight, and consecutive threads still copy consecutive
 // points.
 __global__ __launch_bounds__(BLK) void fill_kernel(const GhostCopy* __restrict__ e, int64_t n, int nf,
                                                    double* __restrict__ U)
 {
-    const int ng = (nf + FC - 1) / FC;
-    for (int64_t t = blockIdx.x * (int64_t)BLK + threadIdx.x; t < n * ng; t += (int64_t)gridDim.x * BLK) {
-        const int64_t gi = t / n;
-        const GhostCopy c = e[t - gi * n];
-        const int f0 = (int)gi * FC;
+    const int f0 = blockIdx.y * FC;
+    for (int64_t t = first_point(); t < n; t += next_point()) {
+        const GhostCopy c = e[t];
         copy_fields(U + c.src + f0 * c.sfs, c.sfs, U + c.dst + f0 * c.dfs, c.dfs, min(FC, nf - f0));
     }
 }
@@ -58,9 +64,9 @@ __global__ __launch_bounds__(BLK) void fill_adjoint_kernel(const GhostSource* __
                                                            const GhostImage* __restrict__ img, int nf,
                                                            double* __restrict__ A)
 {
-    for (int64_t t = blockIdx.x * (int64_t)BLK + threadIdx.x; t < n * nf; t += (int64_t)gridDim.x * BLK) {
-        const int64_t f = t / n;
-        const GhostSource s = src[t - f * n];
+    const int64_t f = blockIdx.y;
+    for (int64_t t = first_point(); t < n; t += next_point()) {
+        const GhostSource s = src[t];
         double acc = A[s.src + f * s.sfs];
         for (int q = s.beg; q < s.end; ++q) {
             const int64_t d = img[q].dst + f * img[q].dfs;
@@ -88,10 +94,9 @@ __global__ __launch_bounds__(BLK) void bor_band_kernel(const GhostCopy* __restri
                                                        const double* __restrict__ k2,
                                                        const double* __restrict__ k3, double* __restrict__ T)
 {
-    const int64_t tot = n * nf;
-    for (int64_t t = blockIdx.x * (int64_t)BLK + threadIdx.x; t < tot; t += (int64_t)gridDim.x * BLK) {
-        const int f = (int)(t / n);
-        const GhostCopy b = band[t - (int64_t)f * n];
+    const int f = blockIdx.y;
+    for (int64_t t = first_point(); t < n; t += next_point()) {
+        const GhostCopy b = band[t];
         const int64_t q = b.src + f * b.sfs;
         T[b.dst + f * b.dfs] = Un[q] + W.w[0] * k0[q] + W.w[1] * k1[q] + W.w[2] * k2[q] + W.w[3] * k3[q];
     }
@@ -224,9 +229,10 @@ __global__ __launch_bounds__(BLK) void prolong_kernel(const ProlongBrick* __rest
 __global__ __launch_bounds__(BLK) void restrict_kernel(const RestrictPt* __restrict__ e, int64_t n, int nf,
                                                        const double* __restrict__ Uf, double* __restrict__ Uc)
 {
-    for (int64_t t = blockIdx.x * (int64_t)BLK + threadIdx.x; t < n; t += (int64_t)gridDim.x * BLK) {
+    const int f0 = blockIdx.y * FC;
+    for (int64_t t = first_point(); t < n; t += next_point()) {
         const RestrictPt r = e[t];
-        copy_fields(Uf + r.f, r.ffs, Uc + r.c, r.cfs, nf);
+        copy_fields(Uf + r.f + f0 * r.ffs, r.ffs, Uc + r.c + f0 * r.cfs, r.cfs, min(FC, nf - f0));
     }
 }
 
@@ -242,7 +248,7 @@ __global__ __launch_bounds__(BLK) void axpby_kernel(int64_t n, double a, const d
 hipError_t launch_fill(const GhostCopy* e, int64_t n, int nf, double* U, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    fill_kernel<<<grid_for(n * ((nf + FC - 1) / FC)), BLK, 0, s>>>(e, n, nf, U);
+    fill_kernel<<<grid_for(n, (nf + FC - 1) / FC), BLK, 0, s>>>(e, n, nf, U);
     return hipGetLastError();
 }
 
@@ -250,7 +256,7 @@ hipError_t launch_fill_adjoint(const GhostSource* src, int64_t n, const GhostIma
                                hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    fill_adjoint_kernel<<<grid_for(n * nf), BLK, 0, s>>>(src, n, img, nf, A);
+    fill_adjoint_kernel<<<grid_for(n, nf), BLK, 0, s>>>(src, n, img, nf, A);
     return hipGetLastError();
 }
 
@@ -265,9 +271,9 @@ __global__ __launch_bounds__(BLK) void radiative_kernel(StageArgs a, PatchDev P,
     const int N[3] = {P.n[0] + 2 * G, P.n[1] + 2 * G, P.n[2] + 2 * G};
     const int64_t S[3] = {1, P.pitch_y, P.pitch_z};
     const double xl[3] = {x0, y0, z0}, i2h = 0.5 / h;
-    for (int64_t t = blockIdx.x * (int64_t)BLK + threadIdx.x; t < n * nf; t += (int64_t)gridDim.x * BLK) {
-        const int f = (int)(t / n);
-        const RadPt q = pts[t - (int64_t)f * n];
+    const int f = blockIdx.y;
+    for (int64_t t = first_point(); t < n; t += next_point()) {
+        const RadPt q = pts[t];
         const int64_t idx = P.off + f * P.fs + q.a[2] * S[2] + q.a[1] * S[1] + q.a[0];
         const double* u = a.Us + idx;
         double x[3], r2 = 0.0;
@@ -297,9 +303,9 @@ __global__ __launch_bounds__(BLK) void radiative_kernel(StageArgs a, PatchDev P,
 __global__ __launch_bounds__(BLK) void copy2_kernel(const GhostCopy* __restrict__ e, int64_t n, int nf,
                                                     const double* __restrict__ src, double* __restrict__ dst)
 {
-    for (int64_t t = blockIdx.x * (int64_t)BLK + threadIdx.x; t < n * nf; t += (int64_t)gridDim.x * BLK) {
-        const int64_t f = t / n;
-        const GhostCopy c = e[t - f * n];
+    const int64_t f = blockIdx.y;
+    for (int64_t t = first_point(); t < n; t += next_point()) {
+        const GhostCopy c = e[t];
         dst[c.dst + f * c.dfs] = src[c.src + f * c.sfs];
     }
 }
@@ -307,7 +313,7 @@ __global__ __launch_bounds__(BLK) void copy2_kernel(const GhostCopy* __restrict_
 hipError_t launch_copy2(const GhostCopy* e, int64_t n, int nf, const double* src, double* dst, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    copy2_kernel<<<grid_for(n * nf), BLK, 0, s>>>(e, n, nf, src, dst);
+    copy2_kernel<<<grid_for(n, nf), BLK, 0, s>>>(e, n, nf, src, dst);
     return hipGetLastError();
 }
 
@@ -315,7 +321,7 @@ hipError_t launch_radiative(const StageArgs& a, const PatchDev& P, const RadPt* 
                             const RadParams& rp, const double xlo[3], double h, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    radiative_kernel<<<grid_for(n * nf), BLK, 0, s>>>(a, P, pts, n, nf, rp, xlo[0], xlo[1], xlo[2], h);
+    radiative_kernel<<<grid_for(n, nf), BLK, 0, s>>>(a, P, pts, n, nf, rp, xlo[0], xlo[1], xlo[2], h);
     return hipGetLastError();
 }
 
@@ -326,7 +332,7 @@ hipError_t launch_bor_band(const GhostCopy* band, int64_t n, int nf, const doubl
     if (n <= 0) return hipSuccess;
     BorW W;
     for (int j = 0; j < 4; ++j) W.w[j] = w[j];
-    bor_band_kernel<<<grid_for(n * nf), BLK, 0, s>>>(band, n, nf, W, Un, k0, k1, k2, k3, T);
+    bor_band_kernel<<<grid_for(n, nf), BLK, 0, s>>>(band, n, nf, W, Un, k0, k1, k2, k3, T);
     return hipGetLastError();
 }
 
@@ -354,7 +360,7 @@ hipError_t launch_prolong(const ProlongBrick* e, int64_t n, const uint32_t* rows
 hipError_t launch_restrict(const RestrictPt* e, int64_t n, int nf, const double* Uf, double* Uc, hipStream_t s)
 {
     if (n <= 0) return hipSuccess;
-    restrict_kernel<<<grid_for(n), BLK, 0, s>>>(e, n, nf, Uf, Uc);
+    restrict_kernel<<<grid_for(n, (nf + FC - 1) / FC), BLK, 0, s>>>(e, n, nf, Uf, Uc);
     return hipGetLastError();
 }
 
