@@ -12,12 +12,18 @@ namespace {
 // WRAP: the patch is the whole periodic domain (at least 4 points per axis)
 // and the neighbours are read at the periodic images of interior points, so
 // that the stage needs no ghost fill; the stencils see the same values.
+// a.swap: the fields change places (Pi takes the part of phi), which makes the
+// stage that of the transposed system.
 template <bool WRAP>
 __global__ __launch_bounds__(256) void wave_stage_kernel(StageArgs a, double ih2, double ko)
 {
     PointRef pr;
     int i, j, k, p;
     if (!tile_point(a, xcd_tile(blockIdx.x, gridDim.x), pr, i, j, k, p)) return;
+    if (a.swap) {
+        pr.c += pr.fs;
+        pr.fs = -pr.fs;
+    }
     const double* phi = a.Us + pr.c;
     const double* pi = phi + pr.fs;
     const int s[3] = {1, pr.sy, pr.sz};
@@ -30,9 +36,8 @@ __global__ __launch_bounds__(256) void wave_stage_kernel(StageArgs a, double ih2
             double vp[7], vq[7];
 #pragma unroll
             for (int o = -3; o <= 3; ++o) {
-                int c = q[d] + o;
-                c = c < 0 ? c + n[d] : (c >= n[d] ? c - n[d] : c);
-                const int64_t off = (int64_t)(c - q[d]) * s[d];
+                const int c = q[d] + o, per = n[d] * s[d];
+                const int off = o * s[d] + (c < 0 ? per : (c >= n[d] ? -per : 0));
                 vp[o + 3] = phi[off];
                 vq[o + 3] = pi[off];
             }
@@ -72,7 +77,11 @@ __global__ __launch_bounds__(WT) void wave_zmarch_kernel(StageArgs a, double ih2
 {
     __shared__ double pl[2][WHY][WPX];
     const Tile tile = a.tiles[xcd_tile(blockIdx.x, gridDim.x)];
-    const PatchDev P = a.patches[tile.patch];
+    PatchDev P = a.patches[tile.patch];
+    if (a.swap) {  // the fields change places
+        P.off += P.fs;
+        P.fs = -P.fs;
+    }
     const int tx = threadIdx.x, ty = threadIdx.y, tid = tx + WX * ty;
     const int x0 = tile.o[0], y0 = tile.o[1], z0 = tile.o[2];
     const int z1 = min(z0 + zc, P.n[2]);

@@ -166,6 +166,11 @@ struct StageArgs {
     // wave stage kernels then read stencil neighbours at the periodic images
     // of interior points and the ghost fill before the stage is skipped
     int wrap;
+    // 1: the wave stage kernels read and write the level's two fields in
+    // exchanged places, which is the stage of the transposed system (the
+    // stencils are symmetric, so d_t (Pi, phi) of the transpose is the forward
+    // right-hand side)
+    int swap;
     // 1 when the driver steps a CCZ4 level that is one periodic patch of at
     // least 2G points per axis: the stage kernel also writes its output at
     // the periodic ghost images of every point within G of a face (faces,

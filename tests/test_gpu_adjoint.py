@@ -99,3 +99,48 @@ def test_gaussian_initial_data_matches_synth():
     ref = synth.wave_gaussian(n, xlo, dx, amp=prm[0], width=prm[1], centre=prm[2:],
                               period=(n[0] * dx, n[1] * dx, n[2] * dx))
     assert np.max(np.abs(got - ref)) < 1e-14
+
+
+@pytest.mark.parametrize("n,boxes", [((64, 64, 64), None),   # marching stage kernel by default
+                                     ((70, 64, 61), None),   # ragged columns, marching set below
+                                     ((20, 12, 9), None), ((12, 9, 1), None), ((3, 5, 4), None),
+                                     ((24, 13, 10), [((0, 0, 0), (10, 12, 9)), ((11, 0, 0), (23, 5, 9)),
+                                                     ((11, 6, 0), (23, 12, 9))])])
+def test_wave_reverse_step_is_the_transposed_step(n, boxes):
+    """The reverse RK4 step of the wave (run as forward stages of the system
+    with its fields exchanged) equals sum_s m_s + lam with m_s from the
+    right-hand side's and the ghost fill's transposes, on one periodic patch
+    (with and without the marching kernel), thin patches and several patches;
+    the ghost entries of lam keep their values.  Tolerance: the two evaluate
+    the same polynomial of degree 4 in other orders, a few dozen roundings of
+    values of the size of lam: 1e-13 of its maximum."""
+    torch = _torch()
+    print("wave reverse", n, boxes, flush=True)
+    dx = 2.0 / max(n)
+    dt = 0.25 * dx
+    levels = [(1, boxes or [((0, 0, 0), tuple(v - 1 for v in n))])]
+    ps = M.Patchset(M.Hierarchy(n, (-1, -1, -1), dx, levels), M.System(M.MOL_WAVE, sigma=0.1))
+    g = torch.Generator(device="cuda").manual_seed(3)
+    lam0 = torch.rand(ps.layouts[0]["nelems"], dtype=torch.float64, device="cuda", generator=g) - 0.5
+    inner = torch.zeros(ps.layouts[0]["nelems"], dtype=torch.bool)
+    for p, (nx, ny, nz) in enumerate(ps.layouts[0]["dims"]):
+        ps._view(0, inner, p, 2)[:, 3:-3, 3:-3, 3:-3] = True
+    inner = inner.cuda()
+    total, m = torch.where(inner, lam0, 0.0), torch.zeros_like(lam0)
+    start = total.clone()
+    for c, b in ((1 / 6, 0.0), (1 / 3, 1.0), (1 / 3, 0.5), (1 / 6, 0.5)):
+        k = dt * (c * start + b * m)
+        m = ps.alloc(0)
+        ps.rhs_adjoint(0, None, k, m)
+        ps.fill_ghosts_adjoint(0, m)
+        m = torch.where(inner, m, 0.0)
+        total = total + m
+    for tiling in (None, (64, 8, 3), (32, 4, 2)):
+        if tiling is not None:
+            ps.set_tiling(0, tiling)
+        lam = lam0.clone()
+        ps.rk4_adjoint_step_stages(0, dt, lam, [ps.alloc(0) for _ in range(3)])
+        torch.cuda.synchronize()
+        assert torch.equal(lam[~inner], lam0[~inner])
+        assert float((lam - total)[inner].abs().max()) < 1e-13
+
