@@ -501,16 +501,27 @@ int build_tiles(const Level& lev, const int td[3], int margin, TileList& tl, Are
 // at least 2^21 points march along z (64 x 8 columns; chunk length for about
 // 512 workgroups, two per compute unit: the fastest measured at 256^3 (64
 // planes) and 512^3 (whole 512-plane columns, no chunk-boundary re-reads));
-// smaller levels use one thread per point.  MHD: 15 x 15 columns, 4 planes.
-void default_tile(int system, int64_t level_points, int td[3])
+// so do levels of at least 2^18 points whose patches fill the columns to 60%
+// (stage on one periodic patch, point-wise against marching: 64^3 9.3 and 7.3
+// us, 80^3 (62% full) 17.7 and 16.1, 96^3 23.1 and 21.6, 120^3 44 and 29; at
+// 48^3, where the columns are 75% full, 7.3 and 7.0, and at 32^3 4.2 and 6.3);
+// other levels use one thread per point.  MHD: 15 x 15 columns, 4 planes.
+void default_tile(int system, const Level& lev, int td[3])
 {
+    int64_t level_points = 0, column_points = 0;
+    for (const PatchDev& pd : lev.pd) {
+        level_points += (int64_t)pd.n[0] * pd.n[1] * pd.n[2];
+        column_points += round_up(pd.n[0], MOL_WAVE_WX) * round_up(pd.n[1], MOL_WAVE_WY) * pd.n[2];
+    }
     switch (system) {
     case MOL_WAVE:
-        if (level_points >= (int64_t(1) << 21)) {
+        if (level_points >= (int64_t(1) << 21) ||
+            (level_points >= (int64_t(1) << 18) && 10 * level_points >= 6 * column_points)) {
             td[0] = MOL_WAVE_WX;
             td[1] = MOL_WAVE_WY;
             td[2] = (int)std::max<int64_t>(
-                4, std::min<int64_t>(MOL_WAVE_ZMAX, level_points / (MOL_WAVE_WX * MOL_WAVE_WY * 512)));
+                level_points >= (int64_t(1) << 21) ? 4 : 2,
+                std::min<int64_t>(MOL_WAVE_ZMAX, level_points / (MOL_WAVE_WX * MOL_WAVE_WY * 512)));
         } else {
             td[0] = 32;
             td[1] = 4;
@@ -853,9 +864,7 @@ int build(mol_patchset* ps, const mol_hierarchy_desc* h, const mol_patchset* pre
             if ((rc = lev.rst.upload(rst, &ps->arena))) return rc;
         }
         int td[3];
-        int64_t npts = 0;
-        for (const PatchDev& pd : lev.pd) npts += (int64_t)pd.n[0] * pd.n[1] * pd.n[2];
-        default_tile(ps->sp.system, npts, td);
+        default_tile(ps->sp.system, lev, td);
         build_tiles(lev, td, 0, lev.tiles, &ps->arena);
         int tg[3] = {MOL_ADJ_GTX, MOL_ADJ_GTY, MOL_ADJ_GTZ};
         build_tiles(lev, tg, G, lev.gtiles, &ps->arena);
