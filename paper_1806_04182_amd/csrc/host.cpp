@@ -458,11 +458,19 @@ struct FineCells {
 // each patch's tiles contiguous; patches in the given order (0: as listed,
 // 1: largest interior first, so that the small patches fill the tail of the
 // launch)
-int build_tiles(const Level& lev, const int td[3], int margin, TileList& tl, Arena* A, int order = 0)
+int build_tiles(const Level& lev, const int shape[3], int margin, TileList& tl, Arena* A, int order = 0,
+                const SysParams* stage = nullptr)
 {
-    tl.tdim[0] = td[0];
-    tl.tdim[1] = td[1];
-    tl.tdim[2] = td[2];
+    // the points a tile covers: the launch shape, except for the MHD kernel
+    // whose workgroups own MHD_CX x MHD_CY columns
+    int td[3] = {shape[0], shape[1], shape[2]};
+    if (stage && (stage->system == MOL_MHD || stage->system == MOL_MHD_GLM) && stage->mhd_flux != MOL_FLUX_SPLIT) {
+        td[0] = MHD_CX;
+        td[1] = MHD_CY;
+    }
+    tl.tdim[0] = shape[0];
+    tl.tdim[1] = shape[1];
+    tl.tdim[2] = shape[2];
     tl.order = order;
     const size_t np = lev.pd.size();
     std::vector<int> perm(np);
@@ -505,9 +513,15 @@ int build_tiles(const Level& lev, const int td[3], int margin, TileList& tl, Are
 // (stage on one periodic patch, point-wise against marching: 64^3 9.3 and 7.3
 // us, 80^3 (62% full) 17.7 and 16.1, 96^3 23.1 and 21.6, 120^3 44 and 29; at
 // 48^3, where the columns are 75% full, 7.3 and 7.0, and at 32^3 4.2 and 6.3);
-// other levels use one thread per point.  MHD: 15 x 15 columns, 4 planes.
-void default_tile(int system, const Level& lev, int td[3])
+// other levels use one thread per point.  MHD: the z chunk that minimises
+// rounds of 256 workgroups (one per compute unit; two for WENO3, whose kernel
+// fits two) times the planes of a chunk and its lead-in (two z reconstructions, 0.7 of a plane; flux splitting: one
+// z flux, 0.35).  Measured at 128^3 (WENO5-Z, LLF) 393 us with chunks of 8
+// (cost 43), 424 with 4 (47), 445 with 16 (50), 487 with 2 (54); at 32^3 24 us
+// with 2 and 40 with 4.
+void default_tile(const SysParams& sp, const Level& lev, int td[3])
 {
+    const int system = sp.system;
     int64_t level_points = 0, column_points = 0;
     for (const PatchDev& pd : lev.pd) {
         level_points += (int64_t)pd.n[0] * pd.n[1] * pd.n[2];
@@ -529,7 +543,24 @@ void default_tile(int system, const Level& lev, int td[3])
         }
         break;
     case MOL_MHD:
-    case MOL_MHD_GLM: td[0] = 15; td[1] = 15; td[2] = 4; break;  // 15 x 15 columns, 4 planes (z-marching)
+    case MOL_MHD_GLM: {
+        const bool split = sp.mhd_flux == MOL_FLUX_SPLIT;
+        const int wx = split ? 15 : MHD_CX, wy = split ? 15 : MHD_CY;
+        const int slots = !split && sp.mhd_recon == MOL_RECON_WENO3 ? 512 : 256;
+        double best = 0.0;
+        for (int zc = 1; zc <= 32; ++zc) {
+            int64_t tiles = 0;
+            for (const PatchDev& pd : lev.pd)
+                tiles += round_up(pd.n[0], wx) / wx * (round_up(pd.n[1], wy) / wy) * (round_up(pd.n[2], zc) / zc);
+            const double cost = (double)((tiles + slots - 1) / slots) * (zc + (split ? 0.35 : 0.7));
+            if (zc == 1 || cost < best) {
+                best = cost;
+                td[2] = zc;
+            }
+        }
+        td[0] = td[1] = 15;  // the shape's name; see MHD_CX
+        break;
+    }
     default: td[0] = MOL_CCZ4_TX; td[1] = MOL_CCZ4_TY; td[2] = MOL_CCZ4_TZ; break;
     }
 }
@@ -864,8 +895,8 @@ int build(mol_patchset* ps, const mol_hierarchy_desc* h, const mol_patchset* pre
             if ((rc = lev.rst.upload(rst, &ps->arena))) return rc;
         }
         int td[3];
-        default_tile(ps->sp.system, lev, td);
-        build_tiles(lev, td, 0, lev.tiles, &ps->arena);
+        default_tile(ps->sp, lev, td);
+        build_tiles(lev, td, 0, lev.tiles, &ps->arena, 0, &ps->sp);
         int tg[3] = {MOL_ADJ_GTX, MOL_ADJ_GTY, MOL_ADJ_GTZ};
         build_tiles(lev, tg, G, lev.gtiles, &ps->arena);
         if (ps->sp.system == MOL_CCZ4) {
@@ -2044,7 +2075,7 @@ std::vector<std::array<int, 3>> tiling_candidates(int system)
         break;
     case MOL_MHD:
     case MOL_MHD_GLM:
-        for (int z : {4, 8, 16, 32}) c.push_back({15, 15, z});
+        for (int z : {1, 2, 4, 6, 8, 16, 32}) c.push_back({15, 15, z});
         break;
     default:
         c.push_back({MOL_CCZ4_TX, MOL_CCZ4_TY, MOL_CCZ4_TZ});
@@ -2076,7 +2107,7 @@ int set_tiles(mol_patchset* ps, int level, const int td[3], int order)
 {
     Level& lev = ps->L[level];
     TileList tl;
-    int rc = build_tiles(lev, td, 0, tl, nullptr, order);
+    int rc = build_tiles(lev, td, 0, tl, nullptr, order, &ps->sp);
     if (rc) {
         tl.dev.release();
         return rc;
@@ -2129,7 +2160,7 @@ int mol_autotune(mol_patchset* ps, int level, const mol_level_state* st, double 
     for (const auto& td : tiling_candidates(ps->sp.system)) {
         for (int order = 0; order <= last_order && rc == MOL_OK; ++order) {
             TileList tl;
-            if ((rc = build_tiles(lev, td.data(), 0, tl, nullptr, order))) break;
+            if ((rc = build_tiles(lev, td.data(), 0, tl, nullptr, order, &ps->sp))) break;
             lev.tiles = tl;
             // RK4 stage 2: reads U, S0 and acc, writes acc and S1
             rc = stage_impl(ps, level, ST_RK4, 2, dt, st->U, st->S0, st->acc, st->S1, nullptr, s, 0, wrap, images);

@@ -105,19 +105,6 @@ constexpr int ORDER[NF] = {GT + 0, GT + 1, GT + 2,   GT + 3,   GT + 4,   GT + 5,
 #define MOL_CCZ4_DMA 1
 #endif
 
-typedef __attribute__((address_space(3))) void lds_void;
-
-// s_waitcnt immediate that waits for all vector-memory loads of this wave
-// (expcnt and lgkmcnt left unconstrained)
-constexpr int VM_WAIT = 0x0F70;
-
-// Workgroup barrier after this wave's LDS accesses have completed.  Unlike
-// __syncthreads() it does not wait for the wave's outstanding vector-memory
-// loads, so LDS-DMA loads of later passes stay in flight across it (the
-// caller waits for the ones the next pass reads); the memory clobber keeps the
-// compiler from moving memory accesses across it.
-__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
-
 template <int TX, int TY, int TZ>
 struct CczLds {
     static constexpr int HX = TX + 2 * G, HY = TY + 2 * G, HZ = TZ + 2 * G;

@@ -18,6 +18,19 @@ __device__ __forceinline__ int xcd_tile(int b, int n)
     return x * per + (x < rem ? x : rem) + slot;
 }
 
+typedef __attribute__((address_space(3))) void lds_void;
+
+// s_waitcnt immediate that waits for all vector-memory operations of this wave
+// (expcnt and lgkmcnt left unconstrained)
+constexpr int VM_WAIT = 0x0F70;
+
+// Workgroup barrier after this wave's LDS accesses have completed.  Unlike
+// __syncthreads() it does not wait for the wave's outstanding vector-memory
+// loads, so LDS-DMA loads of later passes stay in flight across it (the
+// caller waits for the ones the next pass reads); the memory clobber keeps the
+// compiler from moving memory accesses across it.
+__device__ __forceinline__ void lds_barrier() { asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory"); }
+
 // Interior point handled by this thread inside tile `tile`; returns false for
 // the ragged tail.
 struct PointRef {

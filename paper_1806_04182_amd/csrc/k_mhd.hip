@@ -89,7 +89,7 @@ __device__ __forceinline__ double weno3(double v1, double v2, double v3, double 
 }
 
 enum { REC_W5Z = 0, REC_W5JS = 1, REC_W3 = 2 };
-enum { RS_LLF = 0, RS_HLL = 1, RS_SPLIT = 2 };
+enum { RS_LLF = 0, RS_HLL = 1 };
 
 // reconstructed value at the interface to the right of v2 from the left
 template <int REC, bool Q2>
@@ -134,57 +134,102 @@ __device__ __forceinline__ void flux(const double U[8], int d, double gam, doubl
     cf = sqrt(cf2);
 }
 
-// Interface flux between cells 2 and 3 of a six-cell line; get(f, m) returns
-// cell m (0..5) of field f.  Left state reconstructed around cell 2, right
-// state around cell 3 (the left formula on mirrored cells).
-template <int NF, int REC, int RS, bool Q2, class Get>
+// Interface flux by flux splitting between cells 2 and 3 of a six-cell line;
+// get(f, m) returns cell m (0..5) of field f.
+template <int NF, int REC, bool Q2, class Get>
 __device__ __forceinline__ void riemann6(Get get, int d, const MhdConst& C, double Fh[NF])
 {
-    if constexpr (RS == RS_SPLIT) {
-        // (F +- alpha U)/2 of the six cells, alpha the largest signal speed
-        // among them; left-biased reconstruction of the + part around cell 2,
-        // right-biased (mirrored) of the - part around cell 3
-        double gp[NF][6], gm[NF][6], alpha = 0.0;
+    // (F +- alpha U)/2 of the six cells, alpha the largest signal speed
+    // among them; left-biased reconstruction of the + part around cell 2,
+    // right-biased (mirrored) of the - part around cell 3
+    double gp[NF][6], gm[NF][6], alpha = 0.0;
 #pragma unroll
-        for (int m = 0; m < 6; ++m) {
-            double U[NF], F[NF], vd, cf;
+    for (int m = 0; m < 6; ++m) {
+        double U[NF], F[NF], vd, cf;
 #pragma unroll
-            for (int f = 0; f < NF; ++f) U[f] = get(f, m);
-            flux(U, d, C.gam, F, vd, cf);
-            double sp = fabs(vd) + cf;
-            if constexpr (NF == 9) {
-                F[5 + d] += U[8];
-                F[8] = C.ch2 * U[5 + d];
-                sp = fmax(sp, C.ch);
-            }
-            alpha = fmax(alpha, sp);
-#pragma unroll
-            for (int f = 0; f < NF; ++f) {
-                gp[f][m] = F[f];
-                gm[f][m] = U[f];
-            }
+        for (int f = 0; f < NF; ++f) U[f] = get(f, m);
+        flux(U, d, C.gam, F, vd, cf);
+        double sp = fabs(vd) + cf;
+        if constexpr (NF == 9) {
+            F[5 + d] += U[8];
+            F[8] = C.ch2 * U[5 + d];
+            sp = fmax(sp, C.ch);
         }
+        alpha = fmax(alpha, sp);
 #pragma unroll
         for (int f = 0; f < NF; ++f) {
-            double p[6], q[6];
-#pragma unroll
-            for (int m = 0; m < 6; ++m) {
-                p[m] = 0.5 * (gp[f][m] + alpha * gm[f][m]);
-                q[m] = 0.5 * (gp[f][m] - alpha * gm[f][m]);
-            }
-            Fh[f] = recon<REC, Q2>(p[0], p[1], p[2], p[3], p[4], C.eps[d], C.q) +
-                    recon<REC, Q2>(q[5], q[4], q[3], q[2], q[1], C.eps[d], C.q);
+            gp[f][m] = F[f];
+            gm[f][m] = U[f];
         }
-        return;
     }
-    double UL[NF], UR[NF];
 #pragma unroll
     for (int f = 0; f < NF; ++f) {
-        const double c0 = get(f, 0), c1 = get(f, 1), c2 = get(f, 2), c3 = get(f, 3), c4 = get(f, 4),
-                     c5 = get(f, 5);
-        UL[f] = recon<REC, Q2>(c0, c1, c2, c3, c4, C.eps[d], C.q);
-        UR[f] = recon<REC, Q2>(c5, c4, c3, c2, c1, C.eps[d], C.q);
+        double p[6], q[6];
+#pragma unroll
+        for (int m = 0; m < 6; ++m) {
+            p[m] = 0.5 * (gp[f][m] + alpha * gm[f][m]);
+            q[m] = 0.5 * (gp[f][m] - alpha * gm[f][m]);
+        }
+        Fh[f] = recon<REC, Q2>(p[0], p[1], p[2], p[3], p[4], C.eps[d], C.q) +
+                recon<REC, Q2>(q[5], q[4], q[3], q[2], q[1], C.eps[d], C.q);
     }
+}
+
+// Both states that a cell v2 of the line v0 .. v4 contributes: left, at the
+// interface to its right, and right (the left formula on mirrored cells), at
+// the interface to its left.  They share the smoothness indicators and the
+// unnormalised weights: with d_ij = v_j - v_i, 4 beta_r from the second
+// differences a_r and b_r, and X_r = (e_r^2 + tau^2) e_s^2 e_t^2 (WENO5-Z; the
+// factor 4 cancels between them), the left value is v2 plus the weighted mean
+// (3 X_0, 6 X_1, X_2) of the candidates' distances from v2, the right value
+// the same with X_0 and X_2 exchanged.  eps4 = 4 eps (WENO3: eps).
+template <int REC, bool Q2>
+__device__ __forceinline__ void cell_states(double v0, double v1, double v2, double v3, double v4, double eps4, double q,
+                                            double& left, double& right)
+{
+    const double d12 = v2 - v1, d23 = v3 - v2;
+    if constexpr (REC == REC_W3) {
+        const double e0 = fma(d23, d23, eps4), e1 = fma(d12, d12, eps4), s0 = e0 * e0, s1 = e1 * e1;
+        left = v2 + 0.5 * (fma(2.0 * s1, d23, s0 * d12) / fma(2.0, s1, s0));
+        right = v2 - 0.5 * (fma(2.0 * s0, d12, s1 * d23) / fma(2.0, s0, s1));
+        return;
+    }
+    const double d01 = v1 - v0, d34 = v4 - v3;
+    const double a0 = d34 - d23, a1 = d23 - d12, a2 = d12 - d01;
+    const double b0 = fma(-3.0, d23, d34), b1 = d12 + d23, b2 = fma(3.0, d12, -d01);
+    const double c = 13.0 / 3.0;
+    const double be0 = fma(c * a0, a0, b0 * b0), be1 = fma(c * a1, a1, b1 * b1), be2 = fma(c * a2, a2, b2 * b2);
+    const double e0 = eps4 + be0, e1 = eps4 + be1, e2 = eps4 + be2;
+    double X0, X1, X2;
+    if constexpr (REC == REC_W5Z && !Q2) {
+        const double tau = fabs(be0 - be2);
+        X0 = 1.0 + pow(tau / e0, q);
+        X1 = 1.0 + pow(tau / e1, q);
+        X2 = 1.0 + pow(tau / e2, q);
+    } else {
+        const double s0 = e0 * e0, s1 = e1 * e1, s2 = e2 * e2;
+        X0 = s1 * s2;
+        X1 = s0 * s2;
+        X2 = s0 * s1;
+        if constexpr (REC == REC_W5Z) {
+            const double tau = be0 - be2;
+            X0 *= fma(tau, tau, s0);
+            X1 *= fma(tau, tau, s1);
+            X2 *= fma(tau, tau, s2);
+        }
+    }
+    const double t0 = 3.0 * X0, t1 = 6.0 * X1, t2 = 3.0 * X2;
+    const double nl = fma(t0, fma(4.0, d23, -d34), fma(t1, fma(2.0, d23, d12), X2 * fma(5.0, d12, -2.0 * d01)));
+    const double nr = fma(t2, fma(4.0, d12, -d01), fma(t1, fma(2.0, d12, d23), X0 * fma(5.0, d23, -2.0 * d34)));
+    left = fma(1.0 / 6.0, nl / (t0 + t1 + X2), v2);
+    right = fma(-1.0 / 6.0, nr / (t2 + t1 + X0), v2);
+}
+
+// interface flux (LLF or HLL) from the two states
+template <int NF, int RS>
+__device__ __forceinline__ void interface_flux(const double UL[NF], const double UR[NF], int d, const MhdConst& C,
+                                               double Fh[NF])
+{
     double FL[NF], FR[NF], vL, cL, vR, cR;
     flux(UL, d, C.gam, FL, vL, cL);
     flux(UR, d, C.gam, FR, vR, cR);
@@ -213,6 +258,200 @@ __device__ __forceinline__ void riemann6(Get get, int d, const MhdConst& C, doub
     }
 }
 
+// The value of the lane one above (below) in the row of 16 lanes.
+template <int CTRL>
+__device__ __forceinline__ double row_dpp(double v)
+{
+    const int2 u = __builtin_bit_cast(int2, v);
+    int2 r;
+    r.x = __builtin_amdgcn_update_dpp(0, u.x, CTRL, 0xf, 0xf, true);
+    r.y = __builtin_amdgcn_update_dpp(0, u.y, CTRL, 0xf, 0xf, true);
+    return __builtin_bit_cast(double, r);
+}
+constexpr int DPP_FROM_NEXT = 0x101, DPP_FROM_PREV = 0x111;  // row_shl:1, row_shr:1
+
+// LLF and HLL fluxes.  One workgroup of 16 x 16 threads owns a tile of 14 x 16
+// columns and marches along z over zc planes; thread (tx, ty) stands for the
+// cell (tx - 1, ty) of each plane, and along every axis it reconstructs both
+// states of its cell at once (cell_states) and evaluates the flux on the far
+// side of the cell with the near state of the next cell:
+//   z: from a 5-cell register window of the column, the left state and the
+//      flux below carried from the plane before;
+//   x: the next cell is the next lane of the row of 16, so states and fluxes
+//      pass through DPP moves (lanes 0 and 15 are the cells beyond the tile);
+//   y: through LDS; the threads of lanes 0 and 15, which own no column, take
+//      the cells of the rows below and above the tile.
+// The plane with its x/y halo comes into LDS by 16-byte LDS-DMA loads, one
+// plane ahead.  Why cells instead of interfaces: the kernel is bound by FP64
+// issue, and the indicators, most of the reconstruction's arithmetic, are the
+// same for both states of a cell.  Interface by interface before, this after
+// (128^3 stage): WENO5-Z 0.557 -> 0.393 ms, WENO5-JS 0.524 -> 0.380, WENO3 with
+// HLL 0.412 -> 0.250; a sixth of it from requesting a point's stage inputs
+// together (0.488 -> 0.409) and a further 4% from two barriers per plane
+// instead of four.
+// The scheduling barriers keep two fields' reconstructions in flight at a
+// time: without them the kernel spills.  The WENO5 instances take more than
+// 256 registers and run one wave per SIMD without scratch (held to two waves
+// they spill 300 bytes per lane: 0.58 against 0.41 ms at 128^3); WENO3 fits
+// two waves, and two workgroups in a CU's LDS if the exchange along y uses
+// one array and two barriers more (0.25 against 0.30 ms).
+constexpr int CX = MHD_CX, CY = MHD_CY;
+
+template <int NF, int REC, int RS, bool Q2>
+__global__ __launch_bounds__(256, REC == REC_W3 ? 2 : 1) void mhd_cells_kernel(StageArgs a, MhdConst C, int zc)
+{
+    constexpr int H = REC == REC_W3 ? 2 : 3;  // halo: reach of the states of the cells beyond the tile
+    constexpr int CHX = CX + 2 * H, CHY = CY + 2 * H;
+    constexpr bool TWO = REC != REC_W3;
+    __shared__ double pl[2][NF][CHY][CHX];
+    // y exchange, rows -1 .. CY of cells: near states and fluxes.  With two
+    // arrays, two barriers per plane order all uses of LDS: states written |
+    // states read, fluxes written, next plane arrived | fluxes read.
+    __shared__ double ey[NF][CY + 2][CX];
+    __shared__ double fy_[TWO ? NF : 1][CY + 2][CX];
+    auto fy = [&](int f) __attribute__((always_inline)) { return TWO ? fy_[f] : ey[f]; };
+    const Tile tile = a.tiles[xcd_tile(blockIdx.x, gridDim.x)];
+    const PatchDev P = a.patches[tile.patch];
+    const int tx = threadIdx.x, ty = threadIdx.y, tid = tx + 16 * ty;
+    const int x0 = tile.o[0], y0 = tile.o[1], z0 = tile.o[2];
+    const int z1 = min(z0 + zc, P.n[2]);
+    const int64_t fs = P.fs;
+    const int sz = P.pitch_z;
+    const int cx = x0 + tx - 1, cy = y0 + ty;  // this thread's cell
+    const bool col = tx >= 1 && tx <= CX && cx < P.n[0] && cy < P.n[1];
+    // its column (the ghosted box's last one for cells beyond it, which feed
+    // no column of the patch)
+    const double* __restrict__ Us = a.Us;
+    const int64_t colbase = P.off + (int64_t)(min(cy, P.n[1] + G - 1) + G) * P.pitch_y + (min(cx, P.n[0] + G - 1) + G);
+    // cell of the y sweep: its column and row in the tile (rows -1 .. CY)
+    const int yc = tx == 0 || tx == 15 ? min(ty, CX - 1) : tx - 1;
+    const int yr = tx == 0 ? -1 : (tx == 15 ? CY : ty);
+    // LDS-DMA of a plane: one load per field, thread tid the tid-th 16-byte
+    // chunk of the CHY x CHX doubles
+    constexpr int NCH = CHY * CHX / 2;
+    static_assert(NCH <= 256 && CHX % 2 == 0, "one chunk per thread and field");
+    const int hy = tid / (CHX / 2) + G - H, hx = 2 * (tid % (CHX / 2)) + G - H;  // in the ghosted box
+    // (a chunk of the narrower halo starts at an odd column: one that would end
+    // beyond the box holds nothing that is needed)
+    const int doff = x0 + hx + (G - H) % 2 < P.n[0] + 2 * G && y0 + hy < P.n[1] + 2 * G ? hy * P.pitch_y + hx : 0;
+    const int64_t tbase = P.off + (int64_t)y0 * P.pitch_y + x0;
+    auto dma = [&](int k, int b) __attribute__((always_inline)) {
+        const double* src = Us + tbase + (int64_t)(k + G) * sz;
+        if (tid < NCH)
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+                __builtin_amdgcn_global_load_lds((const void*)(src + f * fs + doff),
+                                                 (lds_void*)(&pl[b][f][0][0] + 2 * (tid & ~63)), 16, 0, 0);
+    };
+    double e4[3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) e4[d] = REC == REC_W3 ? C.eps[d] : 4.0 * C.eps[d];
+
+    const StageCoef sc = stage_coef(a);
+    dma(z0, 0);
+    double w[NF][5];             // cells k-1 .. k+3 of the column
+    double ULz[NF], Fz[NF];      // left state of cell k, z flux below cell k
+#pragma unroll
+    for (int f = 0; f < NF; ++f)
+#pragma unroll
+        for (int m = 0; m < 5; ++m) w[f][m] = Us[colbase + f * fs + (int64_t)(z0 - 3 + m + G) * sz];
+    // two lead-in steps bring the left state of cell z0 and the flux below it
+    for (int k = z0 - 2; k < z1; ++k) {
+        const int b = (k - z0) & 1;
+        if (k >= z0 && k + 1 < z1) dma(k + 1, b ^ 1);
+        // ---- z: states of cell k + 1, flux between cells k and k + 1
+        double r[NF];
+        {
+            double UL[NF], UR[NF];
+#pragma unroll
+            for (int f = 0; f < NF; ++f)
+{
+                cell_states<REC, Q2>(w[f][0], w[f][1], w[f][2], w[f][3], w[f][4], e4[2], C.q, UL[f], UR[f]);
+                if (f % 2) __builtin_amdgcn_sched_barrier(0);
+            }
+            if (k >= z0 - 1) {
+                double F[NF];
+                interface_flux<NF, RS>(ULz, UR, 2, C, F);
+#pragma unroll
+                for (int f = 0; f < NF; ++f) {
+                    r[f] = F[f] - Fz[f];
+                    Fz[f] = F[f];
+                }
+            }
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                ULz[f] = UL[f];
+#pragma unroll
+                for (int m = 0; m < 4; ++m) w[f][m] = w[f][m + 1];
+                w[f][4] = k + 1 < z1 ? Us[colbase + f * fs + (int64_t)(k + 4 + G) * sz] : 0.0;
+            }
+        }
+        if (k < z0) continue;
+        if (k == z0) {
+            __builtin_amdgcn_s_waitcnt(VM_WAIT);  // the first plane
+            lds_barrier();
+        }
+        // ---- x
+        {
+            double UL[NF], UR[NF], F[NF];
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                const double* p = &pl[b][f][ty + H][tx + H - 1];
+                cell_states<REC, Q2>(TWO ? p[-2] : 0.0, p[-1], p[0], p[1], TWO ? p[2] : 0.0, e4[0], C.q, UL[f], UR[f]);
+                UR[f] = row_dpp<DPP_FROM_NEXT>(UR[f]);
+                if (f % 2) __builtin_amdgcn_sched_barrier(0);
+            }
+            interface_flux<NF, RS>(UL, UR, 0, C, F);
+#pragma unroll
+            for (int f = 0; f < NF; ++f) r[f] += F[f] - row_dpp<DPP_FROM_PREV>(F[f]);
+        }
+        // ---- y; the stage update's inputs are requested together before the
+        // last exchange (one latency instead of one per field)
+        double pu[NF], pw[NF], psi = 0.0;
+        const int64_t cidx = colbase + (int64_t)(k + G) * sz;
+        {
+            double UL[NF], UR[NF], F[NF];
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                const double* p = &pl[b][f][yr + H][yc + H];
+                cell_states<REC, Q2>(TWO ? p[-2 * CHX] : 0.0, p[-CHX], p[0], p[CHX], TWO ? p[2 * CHX] : 0.0, e4[1], C.q, UL[f],
+                                     UR[f]);
+                ey[f][yr + 1][yc] = UR[f];
+                if (f % 2) __builtin_amdgcn_sched_barrier(0);
+            }
+            if constexpr (NF == 9) psi = pl[b][8][ty + H][tx + H - 1];
+            lds_barrier();
+            const int up = min(yr + 2, CY + 1);
+#pragma unroll
+            for (int f = 0; f < NF; ++f) UR[f] = ey[f][up][yc];
+            if constexpr (!TWO) lds_barrier();
+            interface_flux<NF, RS>(UL, UR, 1, C, F);
+#pragma unroll
+            for (int f = 0; f < NF; ++f) fy(f)[yr + 1][yc] = F[f];
+            __builtin_amdgcn_s_waitcnt(VM_WAIT);  // the next plane
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                pu[f] = sc.pun[cidx + f * fs];
+                pw[f] = sc.pw[cidx + f * fs];
+            }
+            lds_barrier();
+#pragma unroll
+            for (int f = 0; f < NF; ++f) r[f] += F[f] - fy(f)[max(yr, 0)][yc];
+        }
+        if (col) {
+#pragma unroll
+            for (int f = 0; f < NF; ++f) {
+                // psi: the damping source at the cell
+                const double rhs = f == 8 ? -r[f] * C.ih - C.kpsi * psi : -r[f] * C.ih;
+                a.out[cidx + f * fs] = stage_update(a, sc, cidx + f * fs, rhs, pu[f], pw[f]);
+            }
+        }
+        if constexpr (!TWO) lds_barrier();
+    }
+}
+
+// Flux splitting (its reconstruction depends on the interface, so nothing is
+// shared between the states of a cell).
 // One workgroup of 16 x 16 threads owns a tile of 15 x 15 columns and marches
 // along z over ZC planes.  Per plane: the plane (with a 3-cell halo in x and
 // y) is staged in LDS; thread (tx, ty) computes the x-interface flux to the
@@ -227,8 +466,8 @@ constexpr int MB = MT + 1;       // threads per tile edge
 constexpr int MH = MT + 6;       // plane width with halo
 constexpr int MP = MH + 1;       // LDS row pitch
 
-template <int NF, int REC, int RS, bool Q2>
-__global__ __launch_bounds__(MB * MB) void mhd_stage_kernel(StageArgs a, MhdConst C, int zc)
+template <int NF, int REC, bool Q2>
+__global__ __launch_bounds__(MB * MB) void mhd_split_kernel(StageArgs a, MhdConst C, int zc)
 {
     __shared__ double pl[NF][MH][MP];
     __shared__ double fx[NF][MT][MB];
@@ -257,7 +496,7 @@ __global__ __launch_bounds__(MB * MB) void mhd_stage_kernel(StageArgs a, MhdCons
         for (int f = 0; f < NF; ++f)
 #pragma unroll
             for (int m = 0; m < 6; ++m) w[f][m] = c7[f][m + 1];
-        riemann6<NF, REC, RS, Q2>([&](int f, int m) { return c7[f][m]; }, 2, C, Fm);
+        riemann6<NF, REC, Q2>([&](int f, int m) { return c7[f][m]; }, 2, C, Fm);
     }
     for (int k = z0; k < z1; ++k) {
         // stage plane k with its x/y halo
@@ -270,17 +509,17 @@ __global__ __launch_bounds__(MB * MB) void mhd_stage_kernel(StageArgs a, MhdCons
         __syncthreads();
         // x-interface to the left of column (tx, ty): cells tx-3 .. tx+2 of row ty
         double Fp[NF];
-        if (col) riemann6<NF, REC, RS, Q2>([&](int f, int m) { return w[f][m]; }, 2, C, Fp);
+        if (col) riemann6<NF, REC, Q2>([&](int f, int m) { return w[f][m]; }, 2, C, Fp);
         if (ty < MT && x0 + tx <= P.n[0] && y0 + ty < P.n[1]) {
             double F[NF];
-            riemann6<NF, REC, RS, Q2>([&](int f, int m) { return pl[f][ty + G][tx + m]; }, 0, C, F);
+            riemann6<NF, REC, Q2>([&](int f, int m) { return pl[f][ty + G][tx + m]; }, 0, C, F);
 #pragma unroll
             for (int f = 0; f < NF; ++f) fx[f][ty][tx] = F[f];
         }
         // y-interface below column (tx, ty)
         if (tx < MT && y0 + ty <= P.n[1] && x0 + tx < P.n[0]) {
             double F[NF];
-            riemann6<NF, REC, RS, Q2>([&](int f, int m) { return pl[f][ty + m][tx + G]; }, 1, C, F);
+            riemann6<NF, REC, Q2>([&](int f, int m) { return pl[f][ty + m][tx + G]; }, 1, C, F);
 #pragma unroll
             for (int f = 0; f < NF; ++f) fy[f][ty][tx] = F[f];
         }
@@ -312,35 +551,29 @@ __global__ __launch_bounds__(MB * MB) void mhd_stage_kernel(StageArgs a, MhdCons
 template <int NF>
 hipError_t dispatch(const SysParams& sp, const StageArgs& a, const MhdConst& C, int zc, hipStream_t s)
 {
-    const dim3 g(a.ntiles), b(MB, MB, 1);
+    const dim3 g(a.ntiles), b(16, 16, 1);
     const bool hll = sp.mhd_flux == MOL_FLUX_HLL;
+    auto go = [&](auto kernel) { kernel<<<g, b, 0, s>>>(a, C, zc); };
     if (sp.mhd_flux == MOL_FLUX_SPLIT) {
         switch (sp.mhd_recon) {
-        case MOL_RECON_WENO3: mhd_stage_kernel<NF, REC_W3, RS_SPLIT, true><<<g, b, 0, s>>>(a, C, zc); break;
-        case MOL_RECON_WENO5JS: mhd_stage_kernel<NF, REC_W5JS, RS_SPLIT, true><<<g, b, 0, s>>>(a, C, zc); break;
-        default:
-            if (C.q == 2.0) mhd_stage_kernel<NF, REC_W5Z, RS_SPLIT, true><<<g, b, 0, s>>>(a, C, zc);
-            else mhd_stage_kernel<NF, REC_W5Z, RS_SPLIT, false><<<g, b, 0, s>>>(a, C, zc);
+        case MOL_RECON_WENO3: go(mhd_split_kernel<NF, REC_W3, true>); break;
+        case MOL_RECON_WENO5JS: go(mhd_split_kernel<NF, REC_W5JS, true>); break;
+        default: C.q == 2.0 ? go(mhd_split_kernel<NF, REC_W5Z, true>) : go(mhd_split_kernel<NF, REC_W5Z, false>);
         }
         return hipGetLastError();
     }
     switch (sp.mhd_recon) {
     case MOL_RECON_WENO3:
-        if (hll) mhd_stage_kernel<NF, REC_W3, RS_HLL, true><<<g, b, 0, s>>>(a, C, zc);
-        else mhd_stage_kernel<NF, REC_W3, RS_LLF, true><<<g, b, 0, s>>>(a, C, zc);
+        hll ? go(mhd_cells_kernel<NF, REC_W3, RS_HLL, true>) : go(mhd_cells_kernel<NF, REC_W3, RS_LLF, true>);
         break;
     case MOL_RECON_WENO5JS:
-        if (hll) mhd_stage_kernel<NF, REC_W5JS, RS_HLL, true><<<g, b, 0, s>>>(a, C, zc);
-        else mhd_stage_kernel<NF, REC_W5JS, RS_LLF, true><<<g, b, 0, s>>>(a, C, zc);
+        hll ? go(mhd_cells_kernel<NF, REC_W5JS, RS_HLL, true>) : go(mhd_cells_kernel<NF, REC_W5JS, RS_LLF, true>);
         break;
     default:
-        if (C.q == 2.0) {
-            if (hll) mhd_stage_kernel<NF, REC_W5Z, RS_HLL, true><<<g, b, 0, s>>>(a, C, zc);
-            else mhd_stage_kernel<NF, REC_W5Z, RS_LLF, true><<<g, b, 0, s>>>(a, C, zc);
-        } else {
-            if (hll) mhd_stage_kernel<NF, REC_W5Z, RS_HLL, false><<<g, b, 0, s>>>(a, C, zc);
-            else mhd_stage_kernel<NF, REC_W5Z, RS_LLF, false><<<g, b, 0, s>>>(a, C, zc);
-        }
+        if (C.q == 2.0)
+            hll ? go(mhd_cells_kernel<NF, REC_W5Z, RS_HLL, true>) : go(mhd_cells_kernel<NF, REC_W5Z, RS_LLF, true>);
+        else
+            hll ? go(mhd_cells_kernel<NF, REC_W5Z, RS_HLL, false>) : go(mhd_cells_kernel<NF, REC_W5Z, RS_LLF, false>);
     }
     return hipGetLastError();
 }

@@ -26,6 +26,9 @@ constexpr int G = MOL_GHOST;
 #define MOL_CCZ4_TY 8
 #define MOL_CCZ4_TZ 4
 #endif
+// columns per workgroup of the MHD kernel for the LLF and HLL fluxes (the
+// launch shape 15 x 15 x z names its z chunk; flux splitting keeps 15 x 15)
+constexpr int MHD_CX = 14, MHD_CY = 16;
 // minimum waves per SIMD of the CCZ4 kernel
 #ifndef MOL_CCZ4_WAVES
 #define MOL_CCZ4_WAVES 2

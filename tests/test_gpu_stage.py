@@ -414,3 +414,31 @@ def test_ccz4_halo_chunks_at_patch_edges(n, tdim):
     ref = _oracle_steps(O.CCZ4, O.RK4, U0, dx, 0.25 * dx, 1, O.params())
     e = parity_err(got[:, 3:-3, 3:-3, 3:-3], ref[:, 3:-3, 3:-3, 3:-3])
     assert np.all(e <= TOL), e
+
+
+@pytest.mark.parametrize("system", [M.MOL_MHD, M.MOL_MHD_GLM])
+@pytest.mark.parametrize("recon", [M.MOL_RECON_WENO5Z, M.MOL_RECON_WENO5JS, M.MOL_RECON_WENO3])
+@pytest.mark.parametrize("n", [(14, 16, 5), (15, 17, 3), (26, 3, 1), (29, 33, 4)])
+def test_mhd_cell_kernel_tile_edges(n, recon, system):
+    """The MHD kernel that reconstructs both states of a cell, at whole tiles
+    (14 x 16 columns), one column and row more, rows that fill their pitch (26
+    points), one plane and several z chunks, with the LLF and HLL fluxes: one
+    SSP-RK3 step against the oracle; chunks of 1, 2 and 8 planes bit for bit."""
+    torch = _torch()
+    nf = 9 if system == M.MOL_MHD_GLM else 8
+    dx = 1.0 / max(n)
+    st0 = synth.mhd_ot_like(n, seed=5)
+    if nf == 9:
+        st0 = np.concatenate([st0, 1e-2 * st0[1:2]])
+    U0 = synth.embed(st0)
+    osys = O.MHD_GLM if nf == 9 else O.MHD
+    for flux in (M.MOL_FLUX_LLF, M.MOL_FLUX_HLL):
+        print("mhd cells", n, recon, system, flux, flush=True)
+        sysd = M.System(system, sigma=0.0, mhd_recon=recon, mhd_flux=flux, mhd_ch=1.3, mhd_kpsi=0.7)
+        got = [_gpu_steps(osys, M.MOL_SSPRK3, U0, dx, 0.1 * dx, 1, sysd, tiling=(15, 15, zc)) for zc in (1, 2, 8)]
+        assert np.array_equal(got[0], got[1]) and np.array_equal(got[0], got[2])
+        ref = _oracle_steps(osys, O.SSPRK3, U0, dx, 0.1 * dx, 1,
+                            O.params(sigma=0.0, mhd_recon=float(recon), mhd_riemann=float(flux), mhd_ch=1.3, mhd_kpsi=0.7))
+        e = parity_err(got[0][:, 3:-3, 3:-3, 3:-3], ref[:, 3:-3, 3:-3, 3:-3])
+        assert np.all(e <= TOL), e
+
