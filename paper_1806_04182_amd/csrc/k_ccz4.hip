@@ -173,7 +173,10 @@ __device__ constexpr bool single_axis(int f)
 // tidx and its stage update.  buf, buf2: the halo of the field passing
 // through LDS and (LDS-DMA) of the next one; akx: advection + dissipation of
 // every field.
-template <int TX, int TY, int TZ, bool UPWIND>
+// ALL: single-axis fields also load every slot (their few masked lanes save
+// lines, but the branches cost more where a level's tiles do not fill the
+// chip).
+template <int TX, int TY, int TZ, bool UPWIND, bool ALL>
 __device__ __forceinline__ void ccz4_tile(const StageArgs& a, const CczConst& C, int tidx, double* __restrict__ buf,
                                           double* __restrict__ buf2, double (*__restrict__ akx)[TX * TY * TZ])
 {
@@ -357,7 +360,7 @@ __device__ __forceinline__ void ccz4_tile(const StageArgs& a, const CczConst& C,
         const int wbase = tid & ~63;  // first chunk of this wave's window of 64
 #pragma unroll
         for (int r = 0; r < L::NI; ++r)
-            if (single_axis(f) ? ndx[r] : (r + 1) * NT <= L::NCH || r * NT + tid < L::NCH)
+            if (!ALL && single_axis(f) ? ndx[r] : (r + 1) * NT <= L::NCH || r * NT + tid < L::NCH)
                 __builtin_amdgcn_global_load_lds((const void*)(src + doff[r]), (lds_void*)(dst + 2 * (r * NT + wbase)),
                                                  16, 0, 0);
     };
@@ -802,14 +805,14 @@ __device__ __forceinline__ void ccz4_tile(const StageArgs& a, const CczConst& C,
     out(ALP, -alp * alp * (C.f0 + C.f1 / alp) * Kh);
 }
 
-template <int TX, int TY, int TZ, bool UPWIND>
+template <int TX, int TY, int TZ, bool UPWIND, bool ALL = false>
 __global__ __launch_bounds__(TX * TY * TZ, MOL_CCZ4_WAVES) void ccz4_stage_kernel(StageArgs a, CczConst C)
 {
     using L = CczLds<TX, TY, TZ>;
     __shared__ double buf[L::LB];
     __shared__ double buf2[L::DMA ? L::LB : 1];
     __shared__ double akx[NF][L::NT];
-    ccz4_tile<TX, TY, TZ, UPWIND>(a, C, xcd_tile(blockIdx.x, gridDim.x), buf, buf2, akx);
+    ccz4_tile<TX, TY, TZ, UPWIND, ALL>(a, C, xcd_tile(blockIdx.x, gridDim.x), buf, buf2, akx);
 }
 
 }  // namespace
@@ -847,10 +850,17 @@ hipError_t launch_stage_ccz4(const SysParams& sp, const StageArgs& a, const int 
     C.eta = sp.gd_eta;
     if (!dflt) return t888 ? launch_ccz4_tile<8, 8, 8>(sp, a, C, s) : launch_ccz4_tile<8, 4, 8>(sp, a, C, s);
     dim3 blk(MOL_CCZ4_TX, MOL_CCZ4_TY, MOL_CCZ4_TZ);
+    auto go = [&](auto kernel) { kernel<<<a.ntiles, blk, 0, s>>>(a, C); };
+    // at most one workgroup per compute unit: the lines do not matter and the
+    // branches do (stage at 24^3 31.3 -> 30.7 us, 32^3 32.0 -> 31.7; at 48^3,
+    // 432 tiles, masked 42.9 and whole 43.8)
+    const bool all = a.ntiles <= 256;
     if (sp.upwind)
-        ccz4_stage_kernel<MOL_CCZ4_TX, MOL_CCZ4_TY, MOL_CCZ4_TZ, true><<<a.ntiles, blk, 0, s>>>(a, C);
+        all ? go(ccz4_stage_kernel<MOL_CCZ4_TX, MOL_CCZ4_TY, MOL_CCZ4_TZ, true, true>)
+            : go(ccz4_stage_kernel<MOL_CCZ4_TX, MOL_CCZ4_TY, MOL_CCZ4_TZ, true>);
     else
-        ccz4_stage_kernel<MOL_CCZ4_TX, MOL_CCZ4_TY, MOL_CCZ4_TZ, false><<<a.ntiles, blk, 0, s>>>(a, C);
+        all ? go(ccz4_stage_kernel<MOL_CCZ4_TX, MOL_CCZ4_TY, MOL_CCZ4_TZ, false, true>)
+            : go(ccz4_stage_kernel<MOL_CCZ4_TX, MOL_CCZ4_TY, MOL_CCZ4_TZ, false>);
     return hipGetLastError();
 }
 
