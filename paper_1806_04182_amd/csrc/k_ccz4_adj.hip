@@ -19,6 +19,8 @@
 //     them into their owners.
 // The sign branch of the lop-sided stencils is taken from beta at c, as in the
 // forward right-hand side (frozen at U).
+#include <utility>
+
 #include "k_common.h"
 
 namespace mol {
@@ -911,8 +913,17 @@ ADJ_KERNEL(ccz4_adj_chain_kernel)
 
 // ---------------------------------------------------------------- kernel 2
 #ifndef MOL_ADJ_GATHER_GROUP
-#define MOL_ADJ_GATHER_GROUP 13
+#define MOL_ADJ_GATHER_GROUP 5
 #endif
+constexpr int GATHER_GROUPS = (NF + MOL_ADJ_GATHER_GROUP - 1) / MOL_ADJ_GATHER_GROUP;
+
+// stencil weights of the gather (at namespace scope: captured by the sweep
+// they would live in scratch)
+__device__ constexpr double w1[5] = {1.0, -8.0, 0.0, 8.0, -1.0};   // D1: coefficient of u(c+o), o = -2..2
+__device__ constexpr double w2[5] = {-1.0, 16.0, -30.0, 16.0, -1.0};
+__device__ constexpr double wko[7] = {1.0, -6.0, 15.0, -20.0, 15.0, -6.0, 1.0};
+__device__ constexpr double wlp[7] = {0.0, 0.0, -3.0, -10.0, 18.0, -6.0, 1.0};  // beta >= 0: o = -3..3
+__device__ constexpr double wlm[7] = {-1.0, 6.0, -18.0, 10.0, 3.0, 0.0, 0.0};   // beta < 0
 
 // Epilogue of the periodic (WRAP) gather inside a reverse RK4 step: with v the
 // transposed value at p, wsum = v (first) or wsum + v; then either
@@ -980,19 +991,15 @@ __global__ __launch_bounds__(256) void ccz4_adj_gather_kernel(const PatchDev* __
     auto shift = [&](int d, int off) -> int64_t { return (int64_t)tapv(d, off) * S[d]; };
     auto shiftw = [&](int d, int off) -> int64_t { return (int64_t)tapv(d, off) * SW[d]; };
     const bool self = inside(0, 0);
-    const double w1[5] = {1.0, -8.0, 0.0, 8.0, -1.0};   // D1: coefficient of u(c+o), o = -2..2
-    const double w2[5] = {-1.0, 16.0, -30.0, 16.0, -1.0};
-    const double wko[7] = {1.0, -6.0, 15.0, -20.0, 15.0, -6.0, 1.0};
-    const double wlp[7] = {0.0, 0.0, -3.0, -10.0, 18.0, -6.0, 1.0};  // beta >= 0: o = -3..3
-    const double wlm[7] = {-1.0, 6.0, -18.0, 10.0, 3.0, 0.0, 0.0};   // beta < 0
-    // fields in groups of MOL_ADJ_GATHER_GROUP (13: the 25 fields in two
-    // sweeps, at about 150 VGPRs; three sweeps of 9 and one of 25, at 240
-    // VGPRs, measured slower), one accumulator per field of the group; the
-    // taps are swept once per group (rolled loops keep the code small) and
-    // the terms of each field are summed in the same order whatever the
-    // grouping
-#pragma unroll
-    for (int f0 = 0; f0 < NF; f0 += MOL_ADJ_GATHER_GROUP) {
+    // fields in groups of MOL_ADJ_GATHER_GROUP, one workgroup per (tile,
+    // group): one accumulator per field of the group, the taps swept once
+    // (rolled loops keep the code small).  A thread that swept the groups one
+    // after the other (13 fields and 12) left small patches latency bound:
+    // reverse RK4 step at 16^3 791 -> 628 us, 32^3 947 -> 825, 64^3 4645 ->
+    // 4498; at 48^3, where the loads' cache lines bound it, 1884 -> 1870.
+    // Groups of 13, 9, 7 in parallel: 854, 650, 643 us at 16^3.
+    auto sweep = [&](auto gc) __attribute__((always_inline)) {
+        constexpr int f0 = decltype(gc)::value * MOL_ADJ_GATHER_GROUP;
         constexpr int GF = MOL_ADJ_GATHER_GROUP;
         double acc[GF];
 #pragma unroll
@@ -1060,7 +1067,10 @@ __global__ __launch_bounds__(256) void ccz4_adj_gather_kernel(const PatchDev* __
                 }
             }
         }
-    }
+    };
+    [&]<int... Q>(std::integer_sequence<int, Q...>) {
+        (((int)blockIdx.y == Q ? sweep(std::integral_constant<int, Q>{}) : void()), ...);
+    }(std::make_integer_sequence<int, GATHER_GROUPS>{});
 }
 
 AdjConst adj_const(const SysParams& sp)
@@ -1112,7 +1122,7 @@ hipError_t launch_ccz4_adjoint(const SysParams& sp, const PatchDev* patches, con
     }
     if (ngtiles > 0)
         ccz4_adj_gather_kernel<false>
-            <<<ngtiles, dim3(gtd[0], gtd[1], gtd[2]), 0, s>>>(patches, gtiles, U, lam, W, wofs, C, lamU, GatherEpi{});
+            <<<dim3(ngtiles, GATHER_GROUPS), dim3(gtd[0], gtd[1], gtd[2]), 0, s>>>(patches, gtiles, U, lam, W, wofs, C, lamU, GatherEpi{});
     return hipGetLastError();
 }
 
@@ -1129,7 +1139,7 @@ hipError_t launch_ccz4_adjoint_stage(const SysParams& sp, const PatchDev* patche
     AdjConst C = adj_const(sp);
     GatherEpi E{lam0, lam, wsum, wnext, a, b, first, last};
     ccz4_adj_gather_kernel<true>
-        <<<nitiles, dim3(itd[0], itd[1], itd[2]), 0, s>>>(patches, itiles, U, lam_in, W, wofs, C, nullptr, E);
+        <<<dim3(nitiles, GATHER_GROUPS), dim3(itd[0], itd[1], itd[2]), 0, s>>>(patches, itiles, U, lam_in, W, wofs, C, nullptr, E);
     return hipGetLastError();
 }
 
