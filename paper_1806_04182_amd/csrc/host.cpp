@@ -234,6 +234,7 @@ struct mol_patchset {
         TileList ptiles;  // interior tiles for the CCZ4 adjoint's point-wise kernels
         TileList ntiles;  // interior tiles for reductions / initial data
         TileList wtiles;  // interior tiles for the CCZ4 adjoint's periodic gather
+        TileList ctiles;  // interior tiles of the CCZ4 stage kernel's default shape, for the monitors
         // CCZ4 adjoint workspace: start of each patch's block (slots x fs)
         DevArr<int64_t> wofs;
         int64_t wsize = 0;
@@ -244,6 +245,7 @@ struct mol_patchset {
     double* scratch = nullptr;  // reduction partials
     double* tband = nullptr;    // parent-level BOR stage state used by the prolongation
     int red_blocks = 256;
+    int mon_blocks = 512;  // of the monitors: two per compute unit
     hipStream_t capture_stream = nullptr;
 
     ~mol_patchset()
@@ -263,6 +265,7 @@ struct mol_patchset {
             l.wofs.release();
             l.ntiles.dev.release();
             l.wtiles.dev.release();
+            l.ctiles.dev.release();
         }
         rad_pts.release();
         for (auto& t : retired) t.release();
@@ -592,9 +595,9 @@ void reuse_level(mol_patchset* ps, const mol_patchset* prev, int l)
     lev.band_by_patch = o.band_by_patch;
     lev.rst.adopt(o.rst, A);
     lev.rst_by_patch = o.rst_by_patch;
-    TileList* mine[5] = {&lev.tiles, &lev.gtiles, &lev.ntiles, &lev.ptiles, &lev.wtiles};
-    const TileList* theirs[5] = {&o.tiles, &o.gtiles, &o.ntiles, &o.ptiles, &o.wtiles};
-    for (int i = 0; i < 5; ++i) {
+    TileList* mine[6] = {&lev.tiles, &lev.gtiles, &lev.ntiles, &lev.ptiles, &lev.wtiles, &lev.ctiles};
+    const TileList* theirs[6] = {&o.tiles, &o.gtiles, &o.ntiles, &o.ptiles, &o.wtiles, &o.ctiles};
+    for (int i = 0; i < 6; ++i) {
         for (int d = 0; d < 3; ++d) mine[i]->tdim[d] = theirs[i]->tdim[d];
         mine[i]->by_patch = theirs[i]->by_patch;
         mine[i]->count = theirs[i]->count;
@@ -904,6 +907,8 @@ int build(mol_patchset* ps, const mol_hierarchy_desc* h, const mol_patchset* pre
             build_tiles(lev, tp, 0, lev.ptiles, &ps->arena);
             int tw[3] = {MOL_ADJ_WTX, MOL_ADJ_WTY, MOL_ADJ_WTZ};
             build_tiles(lev, tw, 0, lev.wtiles, &ps->arena);
+            int tc[3] = {MOL_CCZ4_TX, MOL_CCZ4_TY, MOL_CCZ4_TZ};
+            build_tiles(lev, tc, 0, lev.ctiles, &ps->arena);
         }
         if (ps->sp.system == MOL_CCZ4) {
             std::vector<int64_t> wo(lev.pd.size());
@@ -919,7 +924,7 @@ int build(mol_patchset* ps, const mol_hierarchy_desc* h, const mol_patchset* pre
         build_tiles(lev, tn, 0, lev.ntiles, &ps->arena);
     }
     // reduction partials: the norms' 5 (8 reserved) or the monitors' per block
-    ps->arena.reserve(sizeof(double) * std::max(8, monitor_partials()) * ps->red_blocks,
+    ps->arena.reserve(sizeof(double) * std::max(8 * ps->red_blocks, monitor_partials() * ps->mon_blocks),
                       reinterpret_cast<void**>(&ps->scratch));
     int64_t tmax = 0;
     for (int l = 0; l + 1 < ps->nlev; ++l) tmax = std::max(tmax, ps->L[l].nelems);
@@ -1733,9 +1738,9 @@ int mol_monitor(mol_patchset* ps, int level, const double* U, uint32_t which, do
     if (pointwise && (pointwise == U)) return fail(MOL_EINVAL, "pointwise must not alias U");
     Level& lev = ps->L[level];
     SysParams sp = level_params(ps, level);
-    hipError_t e = launch_monitor(lev.d_pd.p, lev.ntiles.dev.p, (int)lev.ntiles.dev.n, lev.ntiles.tdim, ps->sp.nf,
-                                  ccz4 ? 1 : 0, which, lev.h, sp.sigma, U, pointwise, ps->scratch, ps->red_blocks,
-                                  out_dev, S(stream));
+    hipError_t e = launch_monitor(lev.d_pd.p, lev.ntiles.dev.p, (int)lev.ntiles.dev.n, lev.ntiles.tdim,
+                                  lev.ctiles.dev.p, (int)lev.ctiles.dev.n, ps->sp.nf, ccz4 ? 1 : 0, which, lev.h,
+                                  sp.sigma, U, pointwise, ps->scratch, ps->mon_blocks, out_dev, S(stream));
     return e == hipSuccess ? MOL_OK : hip_fail(e, "monitor launch");
 }
 

@@ -169,6 +169,16 @@ __device__ constexpr bool single_axis(int f)
     return (f >= KH && f < GH + 3) || f == TH || (f >= BB && f < BB + 3);
 }
 
+// What a monitor launch keeps per thread over the tiles it walks: the
+// reduction's values (sum |v|, sum v^2, max |v| per monitor, then the
+// non-finite fields), and what it needs besides the stage's arguments.
+struct MonSink {
+    unsigned which;
+    double kc, dV;          // sigma / (64 h), cell volume
+    double* point;          // nullable: requested monitors, field k = the k-th
+    double* v;              // value q of thread t at q NT + t, in LDS (38 registers otherwise)
+};
+
 // One tile of the stage: the right-hand side of every interior point of tile
 // tidx and its stage update.  buf, buf2: the halo of the field passing
 // through LDS and (LDS-DMA) of the next one; akx: advection + dissipation of
@@ -176,9 +186,13 @@ __device__ constexpr bool single_axis(int f)
 // ALL: single-axis fields also load every slot (their few masked lanes save
 // lines, but the branches cost more where a level's tiles do not fill the
 // chip).
-template <int TX, int TY, int TZ, bool UPWIND, bool ALL>
+// MON: the constraint monitors instead of the right-hand side (the geometry is
+// the same): no advection, no shift or lapse derivatives, no stage update; the
+// tile's points are added to ms.
+template <int TX, int TY, int TZ, bool UPWIND, bool ALL, bool MON = false>
 __device__ __forceinline__ void ccz4_tile(const StageArgs& a, const CczConst& C, int tidx, double* __restrict__ buf,
-                                          double* __restrict__ buf2, double (*__restrict__ akx)[TX * TY * TZ])
+                                          double* __restrict__ buf2, double (*__restrict__ akx)[TX * TY * TZ],
+                                          MonSink* ms = nullptr)
 {
     using L = CczLds<TX, TY, TZ>;
     constexpr bool DMA = L::DMA;
@@ -186,7 +200,10 @@ __device__ __forceinline__ void ccz4_tile(const StageArgs& a, const CczConst& C,
 
     const Tile tile = a.tiles[tidx];
     const PatchDev P = a.patches[tile.patch];
-    const int tid = threadIdx.x + TX * ((int)threadIdx.y + TY * (int)threadIdx.z);
+    int tid = threadIdx.x + TX * ((int)threadIdx.y + TY * (int)threadIdx.z);
+    // in the monitors' loop over tiles: keeps what follows from tid from being
+    // computed once and held across the tile's passes (280 bytes of scratch)
+    if constexpr (MON) asm volatile("" : "+v"(tid));
     // a wave holds whole rows along the inner row axis
     const int rin = (tid / TX) % L::NIN, rout = tid / (TX * L::NIN);
     const int tx = tid % TX, ty = L::YIN ? rin : rout, tz = L::YIN ? rout : rin;
@@ -360,7 +377,7 @@ __device__ __forceinline__ void ccz4_tile(const StageArgs& a, const CczConst& C,
         const int wbase = tid & ~63;  // first chunk of this wave's window of 64
 #pragma unroll
         for (int r = 0; r < L::NI; ++r)
-            if (!ALL && single_axis(f) ? ndx[r] : (r + 1) * NT <= L::NCH || r * NT + tid < L::NCH)
+            if (!ALL && (MON ? !(f >= GT && f < GT + 6) && f != CHI : single_axis(f)) ? ndx[r] : (r + 1) * NT <= L::NCH || r * NT + tid < L::NCH)
                 __builtin_amdgcn_global_load_lds((const void*)(src + doff[r]), (lds_void*)(dst + 2 * (r * NT + wbase)),
                                                  16, 0, 0);
     };
@@ -401,6 +418,7 @@ __device__ __forceinline__ void ccz4_tile(const StageArgs& a, const CczConst& C,
     double db[3][3], gddb[3], gdiv[3];  // d_k beta^i, gt^jk d_j d_k beta^i, d_i (d_k beta^k)
     double rG[3];                       // Ghat^i terms with d Khat and d Theta
     double alp, A[6], Au[6], Kh, Th, Bv[3];  // point values taken from LDS, At^{ij}
+    [[maybe_unused]] double ko2 = 0.0;       // MON: sum of the fields' squared dissipation terms
     // this point in the halo buffer, its row strides, and the offsets of its
     // x neighbours (LDS-DMA: in the core row or in the wings)
     constexpr int SY = DMA ? (L::YIN ? TX : TX * L::HIN) : PX, SZ = DMA ? (L::YIN ? TX * L::HIN : TX) : PX * HY;
@@ -442,7 +460,8 @@ __device__ __forceinline__ void ccz4_tile(const StageArgs& a, const CczConst& C,
             const double* t = hbuf(q) + ctr;
             // advection beta^k d_k and KO dissipation of every field; first
             // and pure second derivatives from the same combinations
-            constexpr bool second = (f >= GT && f < GT + 6) || f == CHI || f == ALP || (f >= BETA && f < BETA + 3);
+            constexpr bool second =
+                (f >= GT && f < GT + 6) || f == CHI || (!MON && (f == ALP || (f >= BETA && f < BETA + 3)));
             double ak = 0.0, d1v[3], d2v[3];
 #pragma unroll
             for (int k = 0; k < 3; ++k) {
@@ -450,14 +469,21 @@ __device__ __forceinline__ void ccz4_tile(const StageArgs& a, const CczConst& C,
                 const double ko = (x.e3 - 6.0 * x.e2) + 15.0 * x.e1;
                 d1v[k] = 8.0 * x.o1 - x.o2;
                 // explicit fma, so that every tile shape and build rounds alike
-                if (UPWIND)
+                if constexpr (MON)
+                    ak += ko;
+                else if (UPWIND)
                     ak = fma(be[k], fma(10.5, x.o1, fma(0.5, x.o3, -3.0 * x.o2)),
                              fma(fma(0.5, fabs(be[k]), C.koa), ko, ak));
                 else
                     ak = fma(be[k], d1v[k], fma(C.koa, ko, ak));
                 if constexpr (second) d2v[k] = 16.0 * x.e1 - x.e2;
             }
-            akx[f][tid] = C.i12h * ak;
+            if constexpr (MON) {
+                ko2 += (ms->kc * ak) * (ms->kc * ak);
+                if (!isfinite(t[0])) ms->v[(MON_VALUES - 1) * NT + tid] += 1.0;
+            } else {
+                akx[f][tid] = C.i12h * ak;
+            }
 
             auto d1 = [&](int k) __attribute__((always_inline)) { return C.i12h * d1v[k]; };
             auto dd = [&](int k, int l) __attribute__((always_inline)) {
@@ -583,6 +609,7 @@ __device__ __forceinline__ void ccz4_tile(const StageArgs& a, const CczConst& C,
                         Ric[m] += 0.5 * ic * ddc[m] - 0.5 * ic * Gd - 0.25 * ic * ic * dchi[i] * dchi[j] +
                                   2.0 * ic * ic * zs + 0.5 * ic * g[m] * (tr - Ghd);
                     }
+            } else if constexpr (MON && (f == ALP || (f >= BETA && f < BB + 3))) {
             } else if constexpr (f == ALP) {
                 alp = t[0];
 #pragma unroll
@@ -603,7 +630,7 @@ __device__ __forceinline__ void ccz4_tile(const StageArgs& a, const CczConst& C,
                     }
             } else if constexpr (f >= AT && f < AT + 6) {
                 A[f - AT] = t[0];
-                if constexpr (f == AT + 5) {
+                if constexpr (f == AT + 5 && !MON) {
                     // At^{ij} and Gt^i_jk At^jk; the Christoffels are not needed after this
                     double Am[3][3];
 #pragma unroll
@@ -641,22 +668,26 @@ __device__ __forceinline__ void ccz4_tile(const StageArgs& a, const CczConst& C,
                 gddb[i] = s;
             } else if constexpr (f == KH) {
                 Kh = t[0];
-                double d[3];
+                if constexpr (!MON) {
+                    double d[3];
 #pragma unroll
-                for (int k = 0; k < 3; ++k) d[k] = d1(k);
+                    for (int k = 0; k < 3; ++k) d[k] = d1(k);
 #pragma unroll
-                for (int i = 0; i < 3; ++i)
-                    rG[i] = -(2.0 / 3.0) * (gu[SI(i, 0)] * d[0] + gu[SI(i, 1)] * d[1] + gu[SI(i, 2)] * d[2]);
+                    for (int i = 0; i < 3; ++i)
+                        rG[i] = -(2.0 / 3.0) * (gu[SI(i, 0)] * d[0] + gu[SI(i, 1)] * d[1] + gu[SI(i, 2)] * d[2]);
+                }
             } else if constexpr (f == TH) {
                 Th = t[0];
-                double d[3];
+                if constexpr (!MON) {
+                    double d[3];
 #pragma unroll
-                for (int k = 0; k < 3; ++k) d[k] = d1(k);
+                    for (int k = 0; k < 3; ++k) d[k] = d1(k);
 #pragma unroll
-                for (int i = 0; i < 3; ++i)
+                    for (int i = 0; i < 3; ++i)
 #pragma unroll
-                    for (int j = 0; j < 3; ++j)
-                        rG[i] += -gu[SI(i, j)] * ((1.0 / 3.0) * d[j] + Th / alp * dalp[j]);
+                        for (int j = 0; j < 3; ++j)
+                            rG[i] += -gu[SI(i, j)] * ((1.0 / 3.0) * d[j] + Th / alp * dalp[j]);
+                }
             } else if constexpr (f >= BB && f < BB + 3) {
                 Bv[f - BB] = t[0];
             }
@@ -694,8 +725,35 @@ __device__ __forceinline__ void ccz4_tile(const StageArgs& a, const CczConst& C,
         for (int j = 0; j < 3; ++j)
             Am[i][j] = gu[SI(i, 0)] * A[SI(0, j)] + gu[SI(i, 1)] * A[SI(1, j)] + gu[SI(i, 2)] * A[SI(2, j)];
     const double trRic = chi * tr(Ric);
-    const double lapa = chi * tr(DDa);
     const double trA = Am[0][0] + Am[1][1] + Am[2][2];
+    if constexpr (MON) {
+        double AA = 0.0, zz = 0.0;
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                AA += Am[i][j] * Am[j][i];  // At_ij At^ij
+                zz += g[SI(i, j)] * Z[i] * Z[j];
+            }
+        const double mon[MOL_MON_COUNT] = {
+            Th, sqrt(zz / chi), trRic + (2.0 / 3.0) * Kh * Kh + (2.0 / 3.0) * Th * (Kh - 2.0 * Th) - AA, lndet, trA,
+            sqrt(ko2)};
+        int rank = 0;
+#pragma unroll
+        for (int q = 0; q < MOL_MON_COUNT; ++q) {
+            if (!(ms->which >> q & 1u)) continue;
+            const double v = mon[q];
+            if (ms->point) ms->point[c + rank * fs] = v;
+            ++rank;
+            if (!isfinite(v)) continue;
+            double* r = ms->v + 3 * q * NT + tid;
+            r[0] += fabs(v) * ms->dV;
+            r[NT] += v * v * ms->dV;
+            r[2 * NT] = fmax(r[2 * NT], fabs(v));
+        }
+        return;
+    }
+    const double lapa = chi * tr(DDa);
     double AA = 0.0;
 #pragma unroll
     for (int i = 0; i < 3; ++i)
@@ -815,7 +873,63 @@ __global__ __launch_bounds__(TX * TY * TZ, MOL_CCZ4_WAVES) void ccz4_stage_kerne
     ccz4_tile<TX, TY, TZ, UPWIND, ALL>(a, C, xcd_tile(blockIdx.x, gridDim.x), buf, buf2, akx);
 }
 
+// Monitors of a CCZ4 level: the workgroups of an XCD walk its contiguous range
+// of the tile list; each ends with its block's values in partial (fixed order).
+// The kernel streams the fields through LDS like the stage kernel; one thread
+// per point with direct loads of every stencil took 464 registers and 504 us
+// on 101 x 58 x 77 points, this 102 us.
+__global__ __launch_bounds__(256, 2) void ccz4_monitor_kernel(StageArgs a, CczConst C, MonSink init, double* partial)
+{
+    constexpr int TX = MOL_CCZ4_TX, TY = MOL_CCZ4_TY, TZ = MOL_CCZ4_TZ;
+    using L = CczLds<TX, TY, TZ>;
+    static_assert(L::NT == 256, "block reduction over four waves");
+    __shared__ double buf[L::LB];
+    __shared__ double buf2[L::DMA ? L::LB : 1];
+    __shared__ double acc[MON_VALUES * L::NT];
+    const int tid = threadIdx.x + TX * (threadIdx.y + TY * threadIdx.z);
+    MonSink ms = init;
+    ms.v = acc;
+#pragma unroll
+    for (int q = 0; q < MON_VALUES; ++q) acc[q * L::NT + tid] = 0.0;
+    constexpr int NXCD = 8;
+    const int n = a.ntiles, x = blockIdx.x % NXCD, slot = blockIdx.x / NXCD;
+    const int per = n / NXCD, rem = n % NXCD;
+    const int lo = x * per + (x < rem ? x : rem), hi = lo + per + (x < rem ? 1 : 0);
+    const int nwg = ((int)gridDim.x - x + NXCD - 1) / NXCD;  // workgroups of this XCD
+    for (int t = lo + slot; t < hi; t += nwg)
+        ccz4_tile<TX, TY, TZ, false, false, true>(a, C, t, buf, buf2, nullptr, &ms);
+    double r[MON_VALUES];
+#pragma unroll
+    for (int q = 0; q < MON_VALUES; ++q) r[q] = acc[q * L::NT + tid];
+    __syncthreads();  // acc becomes the reduction's LDS
+    mon_block_reduce(r, acc);
+    if (tid == 0)
+        for (int q = 0; q < MON_VALUES; ++q) partial[blockIdx.x * MON_VALUES + q] = r[q];
+}
+
 }  // namespace
+
+hipError_t launch_ccz4_monitor(const PatchDev* patches, const Tile* tiles, int ntiles, unsigned which, double h,
+                               double sigma, const double* U, double* point, double* partial, int nblocks,
+                               hipStream_t s)
+{
+    StageArgs a{};
+    a.patches = patches;
+    a.tiles = tiles;
+    a.ntiles = ntiles;
+    a.Us = U;
+    CczConst C{};
+    C.i12h = 1.0 / (12.0 * h);
+    C.i12h2 = 1.0 / (12.0 * h * h);
+    C.i144h2 = 1.0 / (144.0 * h * h);
+    MonSink m{};
+    m.which = which;
+    m.kc = sigma / (64.0 * h);
+    m.dV = h * h * h;
+    m.point = point;
+    ccz4_monitor_kernel<<<nblocks, dim3(MOL_CCZ4_TX, MOL_CCZ4_TY, MOL_CCZ4_TZ), 0, s>>>(a, C, m, partial);
+    return hipGetLastError();
+}
 
 namespace {
 // the tile shapes compiled besides the default (the autotuner picks one per level)

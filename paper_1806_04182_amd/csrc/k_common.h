@@ -192,6 +192,29 @@ __device__ __forceinline__ double wave_max(double v)
     return v;
 }
 
+// ---- reduction of the monitors' values over a block of four waves: each wave
+// reduces its lanes, lane 0 parks the result in LDS (sh: MON_VALUES x 4), and
+// the wave results are folded in wave order (the same bits on every run)
+constexpr int MON_VALUES = 3 * MOL_MON_COUNT + 1;
+__device__ __forceinline__ bool mon_is_max(int q) { return q < 3 * MOL_MON_COUNT && q % 3 == 2; }
+__device__ __forceinline__ void mon_block_reduce(double v[MON_VALUES], double* sh)
+{
+    const int t = threadIdx.x + blockDim.x * (threadIdx.y + blockDim.y * threadIdx.z);
+    const int lane = t & 63, wv = t >> 6;
+#pragma unroll
+    for (int q = 0; q < MON_VALUES; ++q) {
+        const double w = mon_is_max(q) ? wave_max(v[q]) : wave_sum(v[q]);
+        if (lane == 0) sh[q * 4 + wv] = w;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < MON_VALUES; ++q) {
+        double r = sh[q * 4];
+        for (int w = 1; w < 4; ++w) r = mon_is_max(q) ? fmax(r, sh[q * 4 + w]) : r + sh[q * 4 + w];
+        v[q] = r;
+    }
+}
+
 // ---- 4th-order finite differences, evaluated as differences of symmetric
 // neighbours / differences from the centre so that a small signal on an
 // O(1) background keeps its digits.  Scale factors are applied by callers.

@@ -247,7 +247,12 @@ hipError_t launch_norms(const PatchDev* patches, const Tile* tiles, int ntiles, 
                         const double xlo[3], const CoordBox& box, double* partial, int nblocks, double* out,
                         hipStream_t s);
 int monitor_partials();  // doubles per reduction block of launch_monitor
-hipError_t launch_monitor(const PatchDev* patches, const Tile* tiles, int ntiles, const int td[3], int nf, int ccz4,
+// ctiles: tiles of the CCZ4 stage kernel's default shape (for masks with |Z| or H_Z)
+hipError_t launch_ccz4_monitor(const PatchDev* patches, const Tile* tiles, int ntiles, unsigned which, double h,
+                               double sigma, const double* U, double* point, double* partial, int nblocks,
+                               hipStream_t s);
+hipError_t launch_monitor(const PatchDev* patches, const Tile* tiles, int ntiles, const int td[3], const Tile* ctiles,
+                          int nctiles, int nf, int ccz4,
                           unsigned which, double h, double sigma, const double* U, double* point, double* partial,
                           int nblocks, double* out, hipStream_t s);
 hipError_t launch_puncture(const PatchDev* patches, const Tile* tiles, int ntiles, const int td[3], int nholes,

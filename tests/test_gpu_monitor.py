@@ -141,3 +141,35 @@ def test_monitor_counts_non_finite_values():
     for q, name in enumerate(M.MONITORS):
         for s in range(3):
             assert abs(red[3 * q + s] - ref[name][s]) <= 1e-11 * max(abs(ref[name][s]), 1e-300) + 1e-300, (name, s)
+
+
+@pytest.mark.parametrize("n", [(8, 8, 4), (9, 17, 5), (26, 10, 7), (1, 6, 6)])
+def test_monitor_masks_agree_across_kernels(n):
+    """Masks with |Z| or H_Z run in the tiled kernel, the others in the
+    point-wise one: every single mask gives the point values of the full mask
+    (|Z| and H_Z bit for bit, the others to 1e-14: the two kernels round the
+    determinant and the traces in other orders), the same reductions to the
+    rounding of a sum in another order, and the same results when the level's
+    stage launches take another tile shape; two calls give the same bits."""
+    torch = _torch()
+    print("monitor masks", n, flush=True)
+    dx = 1.0 / max(n)
+    st = synth.ccz4_lapse_pulse(n, (0, 0, 0), dx, amp=0.2, width=0.4)
+    st = st + synth.ccz4_minkowski_noise(n, amp=1e-2, seed=3) - synth.CCZ4_FLAT[:, None, None, None]
+    ps = M.Patchset(M.single_patch(n, (0, 0, 0), dx), M.System(M.MOL_CCZ4))
+    U = torch.from_numpy(ps.pack(0, [synth.embed(st)])).cuda()
+    ps.fill_ghosts(0, U)
+    red, pts = _run(ps, 0, U, M.MOL_MON_ALL)
+    again, _ = _run(ps, 0, U, M.MOL_MON_ALL)
+    assert np.array_equal(red, again) and red[-1] == 0
+    for q in range(M.MOL_MON_COUNT):
+        r, p = _run(ps, 0, U, 1 << q)
+        a, b = p[0][0][3:-3, 3:-3, 3:-3], pts[0][q][3:-3, 3:-3, 3:-3]
+        if (1 << q) & (M.MOL_MON_Z | M.MOL_MON_HZ):
+            assert np.array_equal(a, b)
+        assert np.max(np.abs(a - b)) <= 1e-14 * max(1.0, np.max(np.abs(b)))
+        assert np.all(np.abs(r[3 * q:3 * q + 3] - red[3 * q:3 * q + 3]) <= 1e-12 * np.abs(red[3 * q:3 * q + 3]) + 1e-15)
+    ps.set_tiling(0, (8, 4, 8))
+    other, _ = _run(ps, 0, U, M.MOL_MON_ALL)
+    assert np.array_equal(red, other)
+
