@@ -830,6 +830,10 @@ int build(mol_patchset* ps, const mol_hierarchy_desc* h, const mol_patchset* pre
                                 }
                             }
                 }
+                // in memory order (found in the order of the ghost points'
+                // stencils), so that a wave's loads share cache lines
+                std::sort(band.begin() + lev.band_by_patch[p], band.end(),
+                          [](const GhostCopy& a, const GhostCopy& b) { return a.src < b.src; });
             }
             lev.band_by_patch[lev.pd.size()] = (int64_t)band.size();
             if ((rc = lev.band.upload(band, &ps->arena))) return rc;
