@@ -12,15 +12,15 @@ namespace {
 // WRAP: the patch is the whole periodic domain (at least 4 points per axis)
 // and the neighbours are read at the periodic images of interior points, so
 // that the stage needs no ghost fill; the stencils see the same values.
-// a.swap: the fields change places (Pi takes the part of phi), which makes the
+// SWAP: the fields change places (Pi takes the part of phi), which makes the
 // stage that of the transposed system.
-template <bool WRAP>
+template <bool WRAP, bool SWAP>
 __global__ __launch_bounds__(256) void wave_stage_kernel(StageArgs a, double ih2, double ko)
 {
     PointRef pr;
     int i, j, k, p;
     if (!tile_point(a, xcd_tile(blockIdx.x, gridDim.x), pr, i, j, k, p)) return;
-    if (a.swap) {
+    if constexpr (SWAP) {
         pr.c += pr.fs;
         pr.fs = -pr.fs;
     }
@@ -259,10 +259,12 @@ hipError_t launch_stage_wave(const SysParams& sp, const StageArgs& a, const int 
         else
             a.wrap ? wave_zmarch_kernel<false, true><<<g, b, 0, s>>>(a, ih2, ko, td[2])
                    : wave_zmarch_kernel<false, false><<<g, b, 0, s>>>(a, ih2, ko, td[2]);
-    } else if (a.wrap) {
-        wave_stage_kernel<true><<<a.ntiles, dim3(td[0], td[1], td[2]), 0, s>>>(a, ih2, ko);
     } else {
-        wave_stage_kernel<false><<<a.ntiles, dim3(td[0], td[1], td[2]), 0, s>>>(a, ih2, ko);
+        auto go = [&](auto kernel) { kernel<<<a.ntiles, dim3(td[0], td[1], td[2]), 0, s>>>(a, ih2, ko); };
+        if (a.wrap)
+            a.swap ? go(wave_stage_kernel<true, true>) : go(wave_stage_kernel<true, false>);
+        else
+            a.swap ? go(wave_stage_kernel<false, true>) : go(wave_stage_kernel<false, false>);
     }
     return hipGetLastError();
 }
