@@ -45,7 +45,7 @@ CASES = {
                  "file": "wave_stage_256cube_traffic.json", "workload": "wave 256^3 periodic patch, RK4 stages 1-4"},
     "wave_512": {"prefix": "mol::wave_", "points": 512 ** 3, "sources": ("k_wave.hip",) + COMMON,
                  "file": "wave_stage_512cube_traffic.json", "workload": "wave 512^3 periodic patch, RK4 stages 1-4"},
-    "mhd_128": {"prefix": "mol::mhd_stage_kernel", "points": 128 ** 3, "sources": ("k_mhd.hip",) + COMMON,
+    "mhd_128": {"prefix": "mol::mhd_", "points": 128 ** 3, "sources": ("k_mhd.hip",) + COMMON,
                 "file": "mhd_stage_128cube_traffic.json",
                 "workload": "mhd 128^3 periodic patch (WENO5-Z, LLF), SSP-RK3 stages 1-3"},
 }
