@@ -36,8 +36,9 @@ __global__ __launch_bounds__(256) void wave_stage_kernel(StageArgs a, double ih2
             double vp[7], vq[7];
 #pragma unroll
             for (int o = -3; o <= 3; ++o) {
-                const int c = q[d] + o, per = n[d] * s[d];
-                const int off = o * s[d] + (c < 0 ? per : (c >= n[d] ? -per : 0));
+                int c = q[d] + o;
+                c = c < 0 ? c + n[d] : (c >= n[d] ? c - n[d] : c);
+                const int64_t off = (int64_t)(c - q[d]) * s[d];
                 vp[o + 3] = phi[off];
                 vq[o + 3] = pi[off];
             }
