@@ -457,6 +457,13 @@ struct FineCells {
     }
 };
 
+// whether the level's stage kernel is the MHD one whose workgroups own MHD_CX x
+// MHD_CY columns (LLF and HLL; flux splitting owns 15 x 15)
+bool mhd_cell_columns(const SysParams& sp)
+{
+    return (sp.system == MOL_MHD || sp.system == MOL_MHD_GLM) && sp.mhd_flux != MOL_FLUX_SPLIT;
+}
+
 // tiles of td[0] x td[1] x td[2] points over every patch (grown by margin),
 // each patch's tiles contiguous; patches in the given order (0: as listed,
 // 1: largest interior first, so that the small patches fill the tail of the
@@ -467,7 +474,7 @@ int build_tiles(const Level& lev, const int shape[3], int margin, TileList& tl, 
     // the points a tile covers: the launch shape, except for the MHD kernel
     // whose workgroups own MHD_CX x MHD_CY columns
     int td[3] = {shape[0], shape[1], shape[2]};
-    if (stage && (stage->system == MOL_MHD || stage->system == MOL_MHD_GLM) && stage->mhd_flux != MOL_FLUX_SPLIT) {
+    if (stage && mhd_cell_columns(*stage)) {
         td[0] = MHD_CX;
         td[1] = MHD_CY;
     }
@@ -547,7 +554,7 @@ void default_tile(const SysParams& sp, const Level& lev, int td[3])
         break;
     case MOL_MHD:
     case MOL_MHD_GLM: {
-        const bool split = sp.mhd_flux == MOL_FLUX_SPLIT;
+        const bool split = !mhd_cell_columns(sp);
         const int wx = split ? 15 : MHD_CX, wy = split ? 15 : MHD_CY;
         const int slots = !split && sp.mhd_recon == MOL_RECON_WENO3 ? 512 : 256;
         double best = 0.0;
@@ -597,7 +604,15 @@ void reuse_level(mol_patchset* ps, const mol_patchset* prev, int l)
     lev.rst_by_patch = o.rst_by_patch;
     TileList* mine[6] = {&lev.tiles, &lev.gtiles, &lev.ntiles, &lev.ptiles, &lev.wtiles, &lev.ctiles};
     const TileList* theirs[6] = {&o.tiles, &o.gtiles, &o.ntiles, &o.ptiles, &o.wtiles, &o.ctiles};
-    for (int i = 0; i < 6; ++i) {
+    // MHD with another kind of flux: prev's stage tiles cover other columns
+    // than this system's kernel owns
+    const bool own = mhd_cell_columns(ps->sp) != mhd_cell_columns(prev->sp);
+    if (own) {
+        int td[3];
+        default_tile(ps->sp, lev, td);
+        build_tiles(lev, td, 0, lev.tiles, A, 0, &ps->sp);
+    }
+    for (int i = own ? 1 : 0; i < 6; ++i) {
         for (int d = 0; d < 3; ++d) mine[i]->tdim[d] = theirs[i]->tdim[d];
         mine[i]->by_patch = theirs[i]->by_patch;
         mine[i]->count = theirs[i]->count;

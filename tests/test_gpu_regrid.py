@@ -204,6 +204,33 @@ def test_patchset_from_previous_matches_fresh_build(system):
             np.testing.assert_array_equal(outs[0][l], outs[1][l])
 
 
+@pytest.mark.parametrize("first,then", [(M.MOL_FLUX_LLF, M.MOL_FLUX_SPLIT), (M.MOL_FLUX_SPLIT, M.MOL_FLUX_HLL)])
+def test_patchset_from_previous_with_another_flux(first, then):
+    """mol_create_patchset_from when prev is an MHD patchset on the same boxes
+    with another kind of flux, whose kernel's workgroups own other columns
+    (more than one tile along x and y): one SSP-RK3 step equals the step on a
+    patchset built from scratch, bit for bit."""
+    torch = _torch()
+    n = (33, 35, 6)
+    dx = 1.0 / 35
+    hier = M.Hierarchy(n, (0.0, 0.0, 0.0), dx, [(1, [((0, 0, 0), (16, 34, 5)), ((17, 0, 0), (32, 34, 5))])])
+    prev = M.Patchset(hier, M.System(M.MOL_MHD, sigma=0.0, mhd_flux=first))
+    sysd = M.System(M.MOL_MHD, sigma=0.0, mhd_flux=then)
+    state = synth.mhd_ot_like(n, seed=3)
+    outs = []
+    for ps in (M.Patchset(hier, sysd), M.Patchset(hier, sysd, prev=prev)):
+        print("flux", first, "then", then, flush=True)
+        st = ps.alloc_states()
+        parts = [synth.embed(np.ascontiguousarray(state[:, :, :, :17])),
+                 synth.embed(np.ascontiguousarray(state[:, :, :, 17:]))]
+        st[0]["U"].copy_(torch.from_numpy(ps.pack(0, parts)))
+        ps.advance(st, 0.1 * dx, M.MOL_BATCHED | M.MOL_ADV_SSPRK3)
+        torch.cuda.synchronize()
+        outs.append(ps.unpack(0, st[0]["U"]))
+    for a, b in zip(*outs):
+        np.testing.assert_array_equal(a[:, 3:-3, 3:-3, 3:-3], b[:, 3:-3, 3:-3, 3:-3])
+
+
 def test_two_adaptive_levels_convergence():
     """A second refined level (|phi| >= 1e-2 on level 1) on top of the paper's
     one: n_c at dx0 = 1/40, 1/80, 1/160 with BOR stays near 4 (3.2 rising to
