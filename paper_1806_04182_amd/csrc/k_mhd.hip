@@ -20,7 +20,7 @@ namespace {
 
 struct MhdConst {
     double gam;
-    double eps[3];
+    double eps;
     double q;
     double ih;  // 1 / dx
     double ch2, ch, kpsi;  // cleaning: c_h^2, c_h, kappa_psi
@@ -170,8 +170,8 @@ __device__ __forceinline__ void riemann6(Get get, int d, const MhdConst& C, doub
             p[m] = 0.5 * (gp[f][m] + alpha * gm[f][m]);
             q[m] = 0.5 * (gp[f][m] - alpha * gm[f][m]);
         }
-        Fh[f] = recon<REC, Q2>(p[0], p[1], p[2], p[3], p[4], C.eps[d], C.q) +
-                recon<REC, Q2>(q[5], q[4], q[3], q[2], q[1], C.eps[d], C.q);
+        Fh[f] = recon<REC, Q2>(p[0], p[1], p[2], p[3], p[4], C.eps, C.q) +
+                recon<REC, Q2>(q[5], q[4], q[3], q[2], q[1], C.eps, C.q);
     }
 }
 
@@ -179,10 +179,14 @@ __device__ __forceinline__ void riemann6(Get get, int d, const MhdConst& C, doub
 // interface to its right, and right (the left formula on mirrored cells), at
 // the interface to its left.  They share the smoothness indicators and the
 // unnormalised weights: with d_ij = v_j - v_i, 4 beta_r from the second
-// differences a_r and b_r, and X_r = (e_r^2 + tau^2) e_s^2 e_t^2 (WENO5-Z; the
-// factor 4 cancels between them), the left value is v2 plus the weighted mean
-// (3 X_0, 6 X_1, X_2) of the candidates' distances from v2, the right value
-// the same with X_0 and X_2 exchanged.  eps4 = 4 eps (WENO3: eps).
+// differences a_r and b_r, e_r = 4 (eps + beta_r) and X_r = (e_r^2 + tau^2)
+// e_s^2 e_t^2 (WENO5-Z; the factor 4 cancels between them), the left value is
+// v2 plus the weighted mean (3 X_0, 6 X_1, X_2) of the candidates' distances
+// from v2, the right value the same with X_0 and X_2 exchanged.  The weights
+// carry a common factor K, so that the products with the distances stay finite
+// for all values for which those of d_r / (eps + beta_r)^p times the other
+// denominators with the candidates do (WENO5-Z at jumps of any shape: from
+// 10^22.3 without K to 10^22.8); K costs no operation.  eps4 = 4 eps (WENO3: eps).
 template <int REC, bool Q2>
 __device__ __forceinline__ void cell_states(double v0, double v1, double v2, double v3, double v4, double eps4, double q,
                                             double& left, double& right)
@@ -218,11 +222,12 @@ __device__ __forceinline__ void cell_states(double v0, double v1, double v2, dou
             X2 *= fma(tau, tau, s2);
         }
     }
-    const double t0 = 3.0 * X0, t1 = 6.0 * X1, t2 = 3.0 * X2;
-    const double nl = fma(t0, fma(4.0, d23, -d34), fma(t1, fma(2.0, d23, d12), X2 * fma(5.0, d12, -2.0 * d01)));
-    const double nr = fma(t2, fma(4.0, d12, -d01), fma(t1, fma(2.0, d12, d23), X0 * fma(5.0, d23, -2.0 * d34)));
-    left = fma(1.0 / 6.0, nl / (t0 + t1 + X2), v2);
-    right = fma(-1.0 / 6.0, nr / (t2 + t1 + X0), v2);
+    constexpr double K = 0x1p-20;
+    const double t0 = 3.0 * K * X0, t1 = 6.0 * K * X1, t2 = 3.0 * K * X2;
+    const double nl = fma(t0, fma(4.0, d23, -d34), fma(t1, fma(2.0, d23, d12), X2 * fma(5.0 * K, d12, -2.0 * K * d01)));
+    const double nr = fma(t2, fma(4.0, d12, -d01), fma(t1, fma(2.0, d12, d23), X0 * fma(5.0 * K, d23, -2.0 * K * d34)));
+    left = fma(1.0 / 6.0, nl / fma(K, X2, t0 + t1), v2);
+    right = fma(-1.0 / 6.0, nr / fma(K, X0, t2 + t1), v2);
 }
 
 // interface flux (LLF or HLL) from the two states
@@ -343,9 +348,7 @@ __global__ __launch_bounds__(256, REC == REC_W3 ? 2 : 1) void mhd_cells_kernel(S
                 __builtin_amdgcn_global_load_lds((const void*)(src + f * fs + doff),
                                                  (lds_void*)(&pl[b][f][0][0] + 2 * (tid & ~63)), 16, 0, 0);
     };
-    double e4[3];
-#pragma unroll
-    for (int d = 0; d < 3; ++d) e4[d] = REC == REC_W3 ? C.eps[d] : 4.0 * C.eps[d];
+    const double es = REC == REC_W3 ? C.eps : 4.0 * C.eps;
 
     const StageCoef sc = stage_coef(a);
     dma(z0, 0);
@@ -366,7 +369,7 @@ __global__ __launch_bounds__(256, REC == REC_W3 ? 2 : 1) void mhd_cells_kernel(S
 #pragma unroll
             for (int f = 0; f < NF; ++f)
 {
-                cell_states<REC, Q2>(w[f][0], w[f][1], w[f][2], w[f][3], w[f][4], e4[2], C.q, UL[f], UR[f]);
+                cell_states<REC, Q2>(w[f][0], w[f][1], w[f][2], w[f][3], w[f][4], es, C.q, UL[f], UR[f]);
                 if (f % 2) __builtin_amdgcn_sched_barrier(0);
             }
             if (k >= z0 - 1) {
@@ -397,7 +400,7 @@ __global__ __launch_bounds__(256, REC == REC_W3 ? 2 : 1) void mhd_cells_kernel(S
 #pragma unroll
             for (int f = 0; f < NF; ++f) {
                 const double* p = &pl[b][f][ty + H][tx + H - 1];
-                cell_states<REC, Q2>(TWO ? p[-2] : 0.0, p[-1], p[0], p[1], TWO ? p[2] : 0.0, e4[0], C.q, UL[f], UR[f]);
+                cell_states<REC, Q2>(TWO ? p[-2] : 0.0, p[-1], p[0], p[1], TWO ? p[2] : 0.0, es, C.q, UL[f], UR[f]);
                 UR[f] = row_dpp<DPP_FROM_NEXT>(UR[f]);
                 if (f % 2) __builtin_amdgcn_sched_barrier(0);
             }
@@ -414,7 +417,7 @@ __global__ __launch_bounds__(256, REC == REC_W3 ? 2 : 1) void mhd_cells_kernel(S
 #pragma unroll
             for (int f = 0; f < NF; ++f) {
                 const double* p = &pl[b][f][yr + H][yc + H];
-                cell_states<REC, Q2>(TWO ? p[-2 * CHX] : 0.0, p[-CHX], p[0], p[CHX], TWO ? p[2 * CHX] : 0.0, e4[1], C.q, UL[f],
+                cell_states<REC, Q2>(TWO ? p[-2 * CHX] : 0.0, p[-CHX], p[0], p[CHX], TWO ? p[2 * CHX] : 0.0, es, C.q, UL[f],
                                      UR[f]);
                 ey[f][yr + 1][yc] = UR[f];
                 if (f % 2) __builtin_amdgcn_sched_barrier(0);
@@ -587,7 +590,7 @@ hipError_t launch_stage_mhd(const SysParams& sp, const StageArgs& a, const int t
     C.gam = sp.gamma_ad;
     const double h2 = sp.h * sp.h;
     const double e = sp.weno_eps > 0.0 ? sp.weno_eps : (sp.mhd_recon == MOL_RECON_WENO3 ? h2 : h2 * h2);
-    C.eps[0] = C.eps[1] = C.eps[2] = e;
+    C.eps = e;
     C.q = sp.weno_q;
     C.ih = 1.0 / sp.h;
     if (td[0] != MT || td[1] != MT) return hipErrorInvalidConfiguration;

@@ -442,3 +442,39 @@ def test_mhd_cell_kernel_tile_edges(n, recon, system):
         e = parity_err(got[0][:, 3:-3, 3:-3, 3:-3], ref[:, 3:-3, 3:-3, 3:-3])
         assert np.all(e <= TOL), e
 
+
+
+@pytest.mark.parametrize("recon,scale", [(M.MOL_RECON_WENO5Z, 10.0 ** 22.8), (M.MOL_RECON_WENO5JS, 10.0 ** 33.3),
+                                         (M.MOL_RECON_WENO3, 10.0 ** 61.19)])
+def test_mhd_weights_keep_their_range(recon, scale):
+    """Densities near the largest for which the weights d_r / (eps + beta_r)^p
+    multiplied by the other substencils' denominators stay finite in double
+    precision (products of the sixth power of eps + beta for WENO5-Z, the
+    fourth for WENO5-JS, the second for WENO3): rho, S and E at `scale`, B at
+    its root (the same velocities), jumps of order one between cells.  The
+    right-hand side against the oracle, whose weights form no product."""
+    torch = _torch()
+    n, dx = (20, 18, 9), 1.0 / 20
+    rng = np.random.default_rng(11)
+    base = synth.mhd_ot_like(n, seed=5)
+    st = base.copy()
+    st[0] *= 1.0 + 0.4 * rng.uniform(-1, 1, st[0].shape)
+    st[1:4] *= st[0] / base[0]
+    p = 3.0 * (1.0 + 0.4 * rng.uniform(-1, 1, st[0].shape))
+    st[4] = 0.5 * (st[1:4] ** 2).sum(0) / st[0] + p + 0.5 * (st[5:] ** 2).sum(0)
+    st[:5] *= scale
+    st[5:] *= np.sqrt(scale)
+    U0 = synth.embed(st)
+    O.fill_periodic(U0)
+    for flux in (M.MOL_FLUX_LLF, M.MOL_FLUX_HLL):
+        print("mhd range", recon, flux, flush=True)
+        ps = M.Patchset(M.single_patch(n, (0, 0, 0), dx), M.System(M.MOL_MHD, sigma=0.0, mhd_recon=recon, mhd_flux=flux))
+        U = torch.from_numpy(ps.pack(0, [U0])).cuda()
+        R = ps.alloc(0)
+        ps.rhs(0, U, R)
+        torch.cuda.synchronize()
+        got = ps.unpack(0, R)[0][:, 3:-3, 3:-3, 3:-3]
+        ref = O.rhs(O.MHD, U0, dx, O.params(sigma=0.0, mhd_recon=float(recon), mhd_riemann=float(flux)))[:, 3:-3, 3:-3, 3:-3]
+        assert np.count_nonzero(~np.isfinite(ref)) == 0 and np.count_nonzero(~np.isfinite(got)) == 0
+        e = parity_err(got, ref)
+        assert np.all(e <= TOL), e
