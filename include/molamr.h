@@ -473,10 +473,11 @@ typedef struct {
                     columns along z (z fastest); 3 as 2 with columns in blocks of 2 x 2 */
     double ms;   /* measured time of one stage launch (mol_autotune) */
 } mol_tiling;
-/* Time the batched stage kernel of `level` under every candidate launch shape
- * of the system (wave: z-chunks 4..512 of the z-marching kernel and five
- * thread tiles of the point-wise one; MHD: z-chunks 1..32; CCZ4: tiles
- * 8 x 8 x 4, 8 x 8 x 8 and 8 x 4 x 8) and tile orders (0 and 1; CCZ4 also 2
+/* Time the batched stage kernel of `level` under the level's present tiling,
+ * its default one and every candidate launch shape of the system (wave:
+ * z-chunks 2..512 of the z-marching kernel and five thread tiles of the
+ * point-wise one; MHD: z-chunks 1..32; CCZ4: tiles 8 x 8 x 4, 8 x 8 x 8 and
+ * 8 x 4 x 8) and tile orders (the present one, 0 and 1; CCZ4 also 2
  * and 3), `reps` launches each (RK4 stage 2 with U as
  * U^n, S0 as stage state, acc and S1 overwritten; the kernel variant the
  * driver launches on the level: periodic stencil reads on a wave level that is

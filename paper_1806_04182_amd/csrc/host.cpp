@@ -2090,7 +2090,7 @@ std::vector<std::array<int, 3>> tiling_candidates(int system)
     std::vector<std::array<int, 3>> c;
     switch (system) {
     case MOL_WAVE:
-        for (int z : {4, 8, 16, 32, 64, 128, 256, 512}) c.push_back({MOL_WAVE_WX, MOL_WAVE_WY, z});
+        for (int z : {2, 4, 8, 16, 32, 64, 128, 256, 512}) c.push_back({MOL_WAVE_WX, MOL_WAVE_WY, z});
         c.push_back({32, 4, 2});
         c.push_back({64, 4, 1});
         c.push_back({16, 8, 2});
@@ -2181,33 +2181,44 @@ int mol_autotune(mol_patchset* ps, int level, const mol_level_state* st, double 
     // tile orders: patches as listed or largest first; for CCZ4 also the
     // column orders (the wave and MHD kernels march along z already)
     const int last_order = ps->sp.system == MOL_CCZ4 ? 3 : 1;
-    for (const auto& td : tiling_candidates(ps->sp.system)) {
-        for (int order = 0; order <= last_order && rc == MOL_OK; ++order) {
-            TileList tl;
-            if ((rc = build_tiles(lev, td.data(), 0, tl, nullptr, order, &ps->sp))) break;
-            lev.tiles = tl;
-            // RK4 stage 2: reads U, S0 and acc, writes acc and S1
-            rc = stage_impl(ps, level, ST_RK4, 2, dt, st->U, st->S0, st->acc, st->S1, nullptr, s, 0, wrap, images);
-            if (rc == MOL_OK && (e = hipEventRecord(e0, s)) != hipSuccess) rc = hip_fail(e, "hipEventRecord");
-            for (int r = 0; r < reps && rc == MOL_OK; ++r)
-                rc = stage_impl(ps, level, ST_RK4, 2, dt, st->U, st->S0, st->acc, st->S1, nullptr, s, 0, wrap,
-                                images);
-            float ms = 0.0f;
-            if (rc == MOL_OK && (e = hipEventRecord(e1, s)) != hipSuccess) rc = hip_fail(e, "hipEventRecord");
-            if (rc == MOL_OK && (e = hipEventSynchronize(e1)) != hipSuccess) rc = hip_fail(e, "hipEventSynchronize");
-            if (rc == MOL_OK && (e = hipEventElapsedTime(&ms, e0, e1)) != hipSuccess)
-                rc = hip_fail(e, "hipEventElapsedTime");
-            lev.tiles = keep;
-            tl.dev.release();
-            if (rc) break;
-            const double per = ms / reps;
-            if (win.ms < 0.0 || per < win.ms) {
-                for (int d = 0; d < 3; ++d) win.tdim[d] = td[d];
-                win.order = order;
-                win.ms = per;
-            }
-        }
+    // the level's present tiling first (kept on a tie) and its default one,
+    // which the rules of default_tile may put between the listed shapes
+    std::vector<std::array<int, 3>> shapes = {{keep.tdim[0], keep.tdim[1], keep.tdim[2]}};
+    auto add = [&](const std::array<int, 3>& td) {
+        if (std::find(shapes.begin(), shapes.end(), td) == shapes.end()) shapes.push_back(td);
+    };
+    std::array<int, 3> dflt;
+    default_tile(ps->sp, lev, dflt.data());
+    add(dflt);
+    for (const auto& td : tiling_candidates(ps->sp.system)) add(td);
+    std::vector<std::pair<std::array<int, 3>, int>> cand = {{shapes[0], keep.order}};
+    for (const auto& td : shapes)
+        for (int order = 0; order <= last_order; ++order)
+            if (td != shapes[0] || order != keep.order) cand.emplace_back(td, order);
+    for (const auto& [td, order] : cand) {
+        TileList tl;
+        if ((rc = build_tiles(lev, td.data(), 0, tl, nullptr, order, &ps->sp))) break;
+        lev.tiles = tl;
+        // RK4 stage 2: reads U, S0 and acc, writes acc and S1
+        rc = stage_impl(ps, level, ST_RK4, 2, dt, st->U, st->S0, st->acc, st->S1, nullptr, s, 0, wrap, images);
+        if (rc == MOL_OK && (e = hipEventRecord(e0, s)) != hipSuccess) rc = hip_fail(e, "hipEventRecord");
+        for (int r = 0; r < reps && rc == MOL_OK; ++r)
+            rc = stage_impl(ps, level, ST_RK4, 2, dt, st->U, st->S0, st->acc, st->S1, nullptr, s, 0, wrap,
+                            images);
+        float ms = 0.0f;
+        if (rc == MOL_OK && (e = hipEventRecord(e1, s)) != hipSuccess) rc = hip_fail(e, "hipEventRecord");
+        if (rc == MOL_OK && (e = hipEventSynchronize(e1)) != hipSuccess) rc = hip_fail(e, "hipEventSynchronize");
+        if (rc == MOL_OK && (e = hipEventElapsedTime(&ms, e0, e1)) != hipSuccess)
+            rc = hip_fail(e, "hipEventElapsedTime");
+        lev.tiles = keep;
+        tl.dev.release();
         if (rc) break;
+        const double per = ms / reps;
+        if (win.ms < 0.0 || per < win.ms) {
+            for (int d = 0; d < 3; ++d) win.tdim[d] = td[d];
+            win.order = order;
+            win.ms = per;
+        }
     }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);

@@ -381,6 +381,24 @@ def test_autotuned_tiling_gives_identical_steps(system):
                     np.testing.assert_array_equal(st[l]["U"].cpu().numpy(), want[l], err_msg=f"{tdim} {order} {l}")
 
 
+def test_autotune_times_the_default_tiling():
+    """The default z chunk of an MHD level may lie between the candidates: at
+    72^3 it is 9 (240 workgroups, one round on 256 compute units, against two
+    rounds for 8 or 6), which mol_autotune has to keep."""
+    torch = _torch()
+    print("autotune default", flush=True)
+    n = (72, 72, 72)
+    dx = 1.0 / 72
+    ps = M.Patchset(M.single_patch(n, (0, 0, 0), dx), M.System(M.MOL_MHD, sigma=0.0))
+    st = ps.alloc_states()
+    st[0]["U"].copy_(torch.from_numpy(ps.pack(0, [synth.embed(synth.mhd_ot_like(n, seed=1))])))
+    ps.fill_ghosts(0, st[0]["U"])
+    st[0]["S0"].copy_(st[0]["U"])
+    best = ps.autotune(0, st[0], 0.1 * dx, reps=10)
+    print(best, flush=True)
+    assert best["tdim"] == (15, 15, 9)
+
+
 def test_autotune_cache_records_and_reuses_tilings(tmp_path):
     """autotune_cached: the first patchset tunes every level and records the
     choices in a JSON file keyed by device, library build, system and level
