@@ -393,22 +393,8 @@ __device__ __forceinline__ void ccz4_tile(const StageArgs& a, const CczConst& C,
         Gh[i] = u[(GH + i) * fs];
         be[i] = u[(BETA + i) * fs];
     }
-    double gu[6], lndet;
-    {
-        const double hx = g[0] - 1.0, hy = g[3] - 1.0, hz = g[5] - 1.0;
-        const double hxy = g[1], hxz = g[2], hyz = g[4];
-        const double m2 = hx * hy - hxy * hxy + hx * hz - hxz * hxz + hy * hz - hyz * hyz;
-        const double m3 = hx * (hy * hz - hyz * hyz) - hxy * (hxy * hz - hyz * hxz) + hxz * (hxy * hyz - hy * hxz);
-        const double dm = (hx + hy + hz) + m2 + m3;
-        lndet = log1p(dm);
-        const double idet = 1.0 / (1.0 + dm);
-        gu[0] = (g[3] * g[5] - g[4] * g[4]) * idet;
-        gu[1] = (g[2] * g[4] - g[1] * g[5]) * idet;
-        gu[2] = (g[1] * g[4] - g[2] * g[3]) * idet;
-        gu[3] = (g[0] * g[5] - g[2] * g[2]) * idet;
-        gu[4] = (g[2] * g[1] - g[0] * g[4]) * idet;
-        gu[5] = (g[0] * g[3] - g[1] * g[1]) * idet;
-    }
+    double gu[6];
+    const double lndet = log1p(metric_inverse(g, gu));
 
     // ---- quantities built while the fields stream through LDS ----
     double dg[3][6], lapg[6];           // metric derivatives (until the Christoffels are formed)
@@ -505,7 +491,10 @@ __device__ __forceinline__ void ccz4_tile(const StageArgs& a, const CczConst& C,
             if constexpr (f >= GT && f < GT + 6) {
                 constexpr int qq = f - GT;
 #pragma unroll
-                for (int k = 0; k < 3; ++k) dg[k][qq] = d1(k);
+                for (int k = 0; k < 3; ++k) {
+                    dg[k][qq] = d1(k);
+                    if constexpr (MON) asm("" : "+v"(dg[k][qq]));  // rounded as in the point-wise |Z|
+                }
                 lapg[qq] = trdd();
                 if constexpr (qq == 5) {
                     // Christoffels: Gl[i][jk] = (d_j g_ik + d_k g_ij - d_i g_jk)/2, Gu = gt^-1 Gl
@@ -524,8 +513,10 @@ __device__ __forceinline__ void ccz4_tile(const StageArgs& a, const CczConst& C,
                             Gu[i][m] = gu[SI(i, 0)] * Gl[0][m] + gu[SI(i, 1)] * Gl[1][m] + gu[SI(i, 2)] * Gl[2][m];
 #pragma unroll
                     for (int i = 0; i < 3; ++i) {
-                        const double Gc = gu[0] * Gu[i][0] + gu[3] * Gu[i][3] + gu[5] * Gu[i][5] +
-                                          2.0 * (gu[1] * Gu[i][1] + gu[2] * Gu[i][2] + gu[4] * Gu[i][4]);
+                        const double Gc =
+                            MON ? sym_trace(gu, Gu[i])
+                                : gu[0] * Gu[i][0] + gu[3] * Gu[i][3] + gu[5] * Gu[i][5] +
+                                      2.0 * (gu[1] * Gu[i][1] + gu[2] * Gu[i][2] + gu[4] * Gu[i][4]);
                         Z[i] = 0.5 * chi * (Gh[i] - Gc);
                     }
                     // Rhat_ij without the d Ghat term:

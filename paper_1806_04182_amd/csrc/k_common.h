@@ -215,6 +215,33 @@ __device__ __forceinline__ void mon_block_reduce(double v[MON_VALUES], double* s
     }
 }
 
+// CCZ4: inverse of the conformal metric g (xx xy xz yy yz zz); returns
+// det g - 1, from g - I (no cancellation)
+__device__ __forceinline__ double metric_inverse(const double g[6], double gu[6])
+{
+    const double hx = g[0] - 1.0, hy = g[3] - 1.0, hz = g[5] - 1.0;
+    const double hxy = g[1], hxz = g[2], hyz = g[4];
+    const double m2 = hx * hy - hxy * hxy + hx * hz - hxz * hxz + hy * hz - hyz * hyz;
+    const double m3 = hx * (hy * hz - hyz * hyz) - hxy * (hxy * hz - hyz * hxz) + hxz * (hxy * hyz - hy * hxz);
+    const double dm = (hx + hy + hz) + m2 + m3;
+    const double idet = 1.0 / (1.0 + dm);
+    gu[0] = (g[3] * g[5] - g[4] * g[4]) * idet;
+    gu[1] = (g[2] * g[4] - g[1] * g[5]) * idet;
+    gu[2] = (g[1] * g[4] - g[2] * g[3]) * idet;
+    gu[3] = (g[0] * g[5] - g[2] * g[2]) * idet;
+    gu[4] = (g[2] * g[1] - g[0] * g[4]) * idet;
+    gu[5] = (g[0] * g[3] - g[1] * g[1]) * idet;
+    return dm;
+}
+
+// a^ij b_ij of packed symmetric tensors, in one rounding order whatever code
+// surrounds it (the two kernels with the monitor |Z| give the same bits)
+__device__ __forceinline__ double sym_trace(const double a[6], const double b[6])
+{
+    const double off = fma(a[4], b[4], fma(a[2], b[2], a[1] * b[1]));
+    return fma(2.0, off, fma(a[5], b[5], fma(a[3], b[3], a[0] * b[0])));
+}
+
 // ---- 4th-order finite differences, evaluated as differences of symmetric
 // neighbours / differences from the centre so that a small signal on an
 // O(1) background keeps its digits.  Scale factors are applied by callers.

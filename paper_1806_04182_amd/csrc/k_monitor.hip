@@ -2,9 +2,12 @@
 // the bracket H_Z of the Theta equation, the conformal constraints
 // ln det gt = 0 and tr At = 0; Sec. II.B.1: the size of the KO term),
 // reduced deterministically (fixed tile walk, fixed fold of the block's waves,
-// one final block) like the norms.  Here: the point-wise ones and the KO term,
-// one thread per interior point; a mask with |Z| or H_Z, which need the metric's
-// geometry, goes to the CCZ4 stage kernel's monitor form.
+// one final block) like the norms.  Here: the point-wise ones, the KO term and,
+// where that is faster, |Z|, one thread per interior point; other masks with
+// |Z| or H_Z, which need the metric's geometry, go to the CCZ4 stage kernel's
+// monitor form.
+#include <algorithm>
+
 #include "k_common.h"
 
 namespace mol {
@@ -14,7 +17,11 @@ namespace {
 constexpr int RB = 256;
 constexpr int NQ = MON_VALUES;
 
-// 4th-order dissipation stencil of Sec. II.B.1 along stride s
+// 4th-order stencils of Sec. II.B.1 along stride s: first derivative, dissipation
+__device__ __forceinline__ double d1(const double* u, int64_t s, double i12h)
+{
+    return (8.0 * (u[s] - u[-s]) - (u[2 * s] - u[-2 * s])) * i12h;
+}
 __device__ __forceinline__ double ko(const double* u, int64_t s, double kc)
 {
     const double c = u[0];
@@ -24,7 +31,7 @@ __device__ __forceinline__ double ko(const double* u, int64_t s, double kc)
 }
 
 // CCZ4 field order
-enum { F_GT = 1, F_AT = 8, F_TH = 17 };
+enum { F_CHI = 0, F_GT = 1, F_AT = 8, F_GH = 14, F_TH = 17 };
 __device__ __forceinline__ int sym(int i, int j)
 {
     // xx xy xz yy yz zz
@@ -44,13 +51,16 @@ struct MonArgs {
     double* partial;
 };
 
+// ZED: with |Z|, without the KO term (|Z|'s registers would cost the other
+// masks three waves per SIMD)
+template <bool ZED>
 __global__ __launch_bounds__(RB) void monitor_kernel(MonArgs a)
 {
     __shared__ double sh[NQ * 4];
     double r[NQ];
     for (int q = 0; q < NQ; ++q) r[q] = 0.0;
     const double h = a.h, dV = h * h * h;
-    const double kcoef = a.sigma / (64.0 * h);
+    const double i12h = 1.0 / (12.0 * h), kcoef = a.sigma / (64.0 * h);
     for (int tt = blockIdx.x; tt < a.ntiles; tt += gridDim.x) {
         const Tile t = a.tiles[tt];
         const PatchDev P = a.patches[t.patch];
@@ -62,7 +72,7 @@ __global__ __launch_bounds__(RB) void monitor_kernel(MonArgs a)
         for (int f = 0; f < a.nf; ++f)
             if (!isfinite(U[f * P.fs])) r[3 * MOL_MON_COUNT] += 1.0;
         double mon[MOL_MON_COUNT];
-        if (a.which & MOL_MON_KO) {
+        if (!ZED && (a.which & MOL_MON_KO)) {
             double s = 0.0;
             for (int f = 0; f < a.nf; ++f) {
                 const double* u = U + f * P.fs;
@@ -71,7 +81,7 @@ __global__ __launch_bounds__(RB) void monitor_kernel(MonArgs a)
             }
             mon[5] = sqrt(s);
         }
-        if (a.ccz4 && (a.which & (MOL_MON_THETA | MOL_MON_LNDET | MOL_MON_TRA))) {
+        if (!ZED && a.ccz4 && (a.which & (MOL_MON_THETA | MOL_MON_LNDET | MOL_MON_TRA))) {
             const int64_t fs = P.fs;
             double g[3][3], A[3][3];
             for (int p = 0; p < 3; ++p)
@@ -102,6 +112,55 @@ __global__ __launch_bounds__(RB) void monitor_kernel(MonArgs a)
             double trA = 0.0;
             for (int p = 0; p < 3; ++p)
                 for (int q = 0; q < 3; ++q) trA += gi[p][q] * A[p][q];
+            mon[4] = trA;
+        }
+        if constexpr (ZED) {
+            // the streamed form's operations in its order (asm and sym_trace keep
+            // the compiler from fusing them in another way; the same bits):
+            // dg[m] = d_m gt, Gu[i] = Gt^i_jk
+            const int64_t fs = P.fs;
+            const double chi = U[F_CHI * fs];
+            double g[6], gu[6], A[6], dg[3][6], Gl[3][6], Gu[3][6], Z[3], zz = 0.0, trA = 0.0;
+#pragma unroll
+            for (int q = 0; q < 6; ++q) {
+                g[q] = U[(F_GT + q) * fs];
+                A[q] = U[(F_AT + q) * fs];
+            }
+            const double dm = metric_inverse(g, gu);
+#pragma unroll
+            for (int m = 0; m < 3; ++m)
+#pragma unroll
+                for (int q = 0; q < 6; ++q) {
+                    dg[m][q] = d1(U + (F_GT + q) * fs, st[m], i12h);
+                    asm("" : "+v"(dg[m][q]));
+                }
+#pragma unroll
+            for (int p = 0; p < 3; ++p)
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+#pragma unroll
+                    for (int r = q; r < 3; ++r)
+                        Gl[p][sym(q, r)] = 0.5 * (dg[q][sym(p, r)] + dg[r][sym(p, q)] - dg[p][sym(q, r)]);
+#pragma unroll
+            for (int p = 0; p < 3; ++p)
+#pragma unroll
+                for (int m = 0; m < 6; ++m)
+                    Gu[p][m] = gu[sym(p, 0)] * Gl[0][m] + gu[sym(p, 1)] * Gl[1][m] + gu[sym(p, 2)] * Gl[2][m];
+#pragma unroll
+            for (int p = 0; p < 3; ++p) {
+                const double Gc = sym_trace(gu, Gu[p]);
+                Z[p] = 0.5 * chi * (U[(F_GH + p) * fs] - Gc);
+            }
+#pragma unroll
+            for (int p = 0; p < 3; ++p)
+#pragma unroll
+                for (int q = 0; q < 3; ++q) {
+                    zz += g[sym(p, q)] * Z[p] * Z[q];
+                    trA += gu[sym(p, q)] * A[sym(p, q)];
+                }
+            mon[0] = U[F_TH * fs];
+            mon[1] = sqrt(zz / chi);
+            mon[3] = log1p(dm);
             mon[4] = trA;
         }
         int rank = 0;
@@ -148,11 +207,26 @@ hipError_t launch_monitor(const PatchDev* patches, const Tile* tiles, int ntiles
                           int nblocks, double* out, hipStream_t s)
 {
     hipError_t e;
-    if (ccz4 && (which & (MOL_MON_Z | MOL_MON_HZ))) {
+    const bool z = ccz4 && (which & MOL_MON_Z);
+    // |Z| without H_Z and the KO term reads six fields' first derivatives, but
+    // the streamed form passes all 25 fields: point-wise on levels of at most
+    // one streamed tile per two compute units, which wait for the passes (8^3
+    // to 32^3 points 20 against 32 us, 40^3 41 and 33), and where the point-wise
+    // tiles are no more (whole rows of 32: 64^3 57 and 67 us, 96^3 153 and 182;
+    // elsewhere, 80^3: 124 and 115, 64 patches of 16^3: 102 and 67)
+    const bool direct = z && !(which & (MOL_MON_HZ | MOL_MON_KO)) && (nctiles <= 128 || ntiles <= nctiles);
+    const bool stream = ccz4 && (which & (MOL_MON_Z | MOL_MON_HZ)) && !direct;
+    // one block per tile up to nblocks, two per compute unit (|Z| point-wise
+    // takes a compute unit: half as many; the streamed form walks the tiles by
+    // XCD: a block for each of the eight).  More blocks than tiles cost the
+    // final fold: wave 8^3 17.3 -> 15.7 us with 8 instead of 512
+    nblocks = stream ? std::clamp(nctiles, 8, nblocks) : std::clamp(ntiles, 1, direct ? nblocks / 2 : nblocks);
+    if (stream) {
         e = launch_ccz4_monitor(patches, ctiles, nctiles, which, h, sigma, U, point, partial, nblocks, s);
     } else {
         MonArgs a{patches, tiles, ntiles, nf, ccz4, which, h, sigma, U, point, partial};
-        monitor_kernel<<<nblocks, dim3(td[0], td[1], td[2]), 0, s>>>(a);
+        const dim3 b(td[0], td[1], td[2]);
+        z ? monitor_kernel<true><<<nblocks, b, 0, s>>>(a) : monitor_kernel<false><<<nblocks, b, 0, s>>>(a);
         e = hipGetLastError();
     }
     if (e != hipSuccess) return e;

@@ -173,3 +173,29 @@ def test_monitor_masks_agree_across_kernels(n):
     other, _ = _run(ps, 0, U, M.MOL_MON_ALL)
     assert np.array_equal(red, other)
 
+
+
+@pytest.mark.parametrize("n", [(32, 32, 32), (33, 32, 32), (64, 16, 36), (65, 16, 36), (3, 2, 1)])
+def test_z_monitor_at_the_edges_of_its_dispatch(n):
+    """|Z| without H_Z and the KO term is evaluated point-wise on levels of at
+    most 128 streamed tiles (32^3) or where the point-wise tiles are no more
+    (64 x 16 x 36: 144 of each), in the streamed form otherwise: against the
+    oracle, and bit for bit the full mask's point values."""
+    torch = _torch()
+    print("z monitor", n, flush=True)
+    dx = 1.0 / max(n)
+    st = synth.ccz4_lapse_pulse(n, (0, 0, 0), dx, amp=0.2, width=0.4)
+    st = st + synth.ccz4_minkowski_noise(n, amp=1e-2, seed=3) - synth.CCZ4_FLAT[:, None, None, None]
+    U0 = synth.embed(st)
+    O.fill_periodic(U0)
+    ps = M.Patchset(M.single_patch(n, (0, 0, 0), dx), M.System(M.MOL_CCZ4))
+    U = torch.from_numpy(ps.pack(0, [U0])).cuda()
+    _, full = _run(ps, 0, U, M.MOL_MON_ALL)
+    ref = O.monitor(O.CCZ4, U0, dx)
+    which = M.MOL_MON_THETA | M.MOL_MON_Z | M.MOL_MON_TRA
+    red, pts = _run(ps, 0, U, which)
+    _compare(pts[0], red, ref, which, dx ** 3)
+    _reductions_match(red, {k: [v] for k, v in ref.items()}, which, dx ** 3)
+    again, _ = _run(ps, 0, U, which)
+    assert np.array_equal(red, again)
+    assert np.array_equal(pts[0][1][3:-3, 3:-3, 3:-3], full[0][1][3:-3, 3:-3, 3:-3])
