@@ -912,10 +912,8 @@ ADJ_KERNEL(ccz4_adj_chain_kernel)
 }
 
 // ---------------------------------------------------------------- kernel 2
-#ifndef MOL_ADJ_GATHER_GROUP
-#define MOL_ADJ_GATHER_GROUP 5
-#endif
-constexpr int GATHER_GROUPS = (NF + MOL_ADJ_GATHER_GROUP - 1) / MOL_ADJ_GATHER_GROUP;
+// groups of gf fields of the gather
+constexpr int gather_groups(int gf) { return (NF + gf - 1) / gf; }
 
 // stencil weights of the gather (at namespace scope: captured by the sweep
 // they would live in scratch)
@@ -943,7 +941,7 @@ struct GatherEpi {
 // axis): every interior point p, with the stencil points c taken at their
 // periodic images, so no ghost entry arises; the result goes through the
 // epilogue instead of lamU.
-template <bool WRAP>
+template <bool WRAP, int GF>
 __global__ __launch_bounds__(256) void ccz4_adj_gather_kernel(const PatchDev* __restrict__ patches,
                                                               const Tile* __restrict__ tiles,
                                                               const double* __restrict__ Ug,
@@ -991,16 +989,15 @@ __global__ __launch_bounds__(256) void ccz4_adj_gather_kernel(const PatchDev* __
     auto shift = [&](int d, int off) -> int64_t { return (int64_t)tapv(d, off) * S[d]; };
     auto shiftw = [&](int d, int off) -> int64_t { return (int64_t)tapv(d, off) * SW[d]; };
     const bool self = inside(0, 0);
-    // fields in groups of MOL_ADJ_GATHER_GROUP, one workgroup per (tile,
-    // group): one accumulator per field of the group, the taps swept once
-    // (rolled loops keep the code small).  A thread that swept the groups one
-    // after the other (13 fields and 12) left small patches latency bound:
-    // reverse RK4 step at 16^3 791 -> 628 us, 32^3 947 -> 825, 64^3 4645 ->
-    // 4498; at 48^3, where the loads' cache lines bound it, 1884 -> 1870.
-    // Groups of 13, 9, 7 in parallel: 854, 650, 643 us at 16^3.
+    // fields in groups of GF, one workgroup per (tile, group): one accumulator
+    // per field of the group, the taps swept once (rolled loops keep the code
+    // small).  A thread that swept 13 fields and then 12 left small patches
+    // latency bound: reverse RK4 step (periodic) at 16^3 791 us, with groups
+    // of 5 628, 32^3 947 and 825, 64^3 4645 and 4498; at 48^3, where the loads'
+    // cache lines bound it, 1884 and 1870.  Groups of 13, 9, 7 in parallel: 854,
+    // 650, 643 us at 16^3.
     auto sweep = [&](auto gc) __attribute__((always_inline)) {
-        constexpr int f0 = decltype(gc)::value * MOL_ADJ_GATHER_GROUP;
-        constexpr int GF = MOL_ADJ_GATHER_GROUP;
+        constexpr int f0 = decltype(gc)::value * GF;
         double acc[GF];
 #pragma unroll
         for (int g = 0; g < GF; ++g)
@@ -1070,7 +1067,7 @@ __global__ __launch_bounds__(256) void ccz4_adj_gather_kernel(const PatchDev* __
     };
     [&]<int... Q>(std::integer_sequence<int, Q...>) {
         (((int)blockIdx.y == Q ? sweep(std::integral_constant<int, Q>{}) : void()), ...);
-    }(std::make_integer_sequence<int, GATHER_GROUPS>{});
+    }(std::make_integer_sequence<int, gather_groups(GF)>{});
 }
 
 AdjConst adj_const(const SysParams& sp)
@@ -1120,9 +1117,18 @@ hipError_t launch_ccz4_adjoint(const SysParams& sp, const PatchDev* patches, con
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    if (ngtiles > 0)
-        ccz4_adj_gather_kernel<false>
-            <<<dim3(ngtiles, GATHER_GROUPS), dim3(gtd[0], gtd[1], gtd[2]), 0, s>>>(patches, gtiles, U, lam, W, wofs, C, lamU, GatherEpi{});
+    if (ngtiles > 0) {
+        const dim3 b(gtd[0], gtd[1], gtd[2]);
+        // groups of 5 as long as the launch is short of waves, 13 beyond (fewer
+        // loads of the shared taps): right-hand-side adjoint of 264 tiles (four
+        // patches of 16^3) 189 and 193 us, of 380 (32^3) 233 and 222, of 960
+        // (eight of 24^3) 685 and 663, of 6048 (eight of 48^3) 3832 and 3696
+        auto go = [&](auto kernel, int gf) {
+            kernel<<<dim3(ngtiles, gather_groups(gf)), b, 0, s>>>(patches, gtiles, U, lam, W, wofs, C, lamU,
+                                                                  GatherEpi{});
+        };
+        ngtiles <= 320 ? go(ccz4_adj_gather_kernel<false, 5>, 5) : go(ccz4_adj_gather_kernel<false, 13>, 13);
+    }
     return hipGetLastError();
 }
 
@@ -1138,8 +1144,9 @@ hipError_t launch_ccz4_adjoint_stage(const SysParams& sp, const PatchDev* patche
     if (e != hipSuccess || nitiles <= 0) return e;
     AdjConst C = adj_const(sp);
     GatherEpi E{lam0, lam, wsum, wnext, a, b, first, last};
-    ccz4_adj_gather_kernel<true>
-        <<<dim3(nitiles, GATHER_GROUPS), dim3(itd[0], itd[1], itd[2]), 0, s>>>(patches, itiles, U, lam_in, W, wofs, C, nullptr, E);
+    ccz4_adj_gather_kernel<true, 5>
+        <<<dim3(nitiles, gather_groups(5)), dim3(itd[0], itd[1], itd[2]), 0, s>>>(
+            patches, itiles, U, lam_in, W, wofs, C, nullptr, E);
     return hipGetLastError();
 }
 

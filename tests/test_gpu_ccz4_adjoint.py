@@ -210,3 +210,37 @@ def test_rhs_adjoint_on_a_level_of_ragged_patches_matches_oracle():
     sc = np.maximum(np.max(np.abs(ref), axis=(1, 2, 3)), 1.0)
     err = np.max(np.abs(got - ref), axis=(1, 2, 3)) / sc
     assert np.all(err < 1e-12), err
+
+
+def test_rhs_adjoint_gather_groups_agree():
+    """The gather's groups of 5 fields (one patch of 28^3, 306 tiles) and of 13
+    (the same box in eight patches of 14^3, 400 tiles): the same derivative to
+    the rounding of ghost entries folded in another order, and the dot-product
+    identity with the oracle's Jacobian-vector product."""
+    torch = _torch()
+    n, dx, G = (28, 28, 28), 2.0 / 28, 3
+    U = _state(n, dx, 17)
+    rng = np.random.default_rng(8)
+    lam, v = rng.standard_normal((25, 28, 28, 28)), rng.standard_normal((25, 28, 28, 28))
+    one = _gpu_vjp(M.Patchset(M.single_patch(n, (-1, -1, -1), dx), M.System(M.MOL_CCZ4)), U, lam)
+    boxes = [((i, j, k), (i + 13, j + 13, k + 13)) for k in (0, 14) for j in (0, 14) for i in (0, 14)]
+    ps = M.Patchset(M.Hierarchy(n, (-1, -1, -1), dx, [(1, boxes)]), M.System(M.MOL_CCZ4))
+    cut = lambda a, lo, hi, g: a[:, lo[2]:hi[2] + 1 + g, lo[1]:hi[1] + 1 + g, lo[0]:hi[0] + 1 + g]
+    Ud = torch.from_numpy(ps.pack(0, [cut(U, lo, hi, 2 * G).copy() for lo, hi in boxes])).cuda()
+    Ld = torch.from_numpy(ps.pack(0, [synth.embed(cut(lam, lo, hi, 0)) for lo, hi in boxes])).cuda()
+    out = ps.alloc(0)
+    ps.rhs_adjoint(0, Ud, Ld, out, ps.alloc_work(0))
+    ps.fill_ghosts_adjoint(0, out)
+    torch.cuda.synchronize()
+    got = np.zeros_like(one)
+    for (lo, hi), a in zip(boxes, ps.unpack(0, out)):
+        cut(got, lo, hi, 0)[...] = synth.interior(a)
+    sc = np.maximum(np.max(np.abs(one), axis=(1, 2, 3)), 1.0)
+    assert np.all(np.max(np.abs(got - one), axis=(1, 2, 3)) / sc < 1e-12)
+    V = synth.embed(v)
+    O.fill_periodic(V)
+    _, JV = O.ccz4_rhs_jvp(U, V, dx)
+    b = np.sum(lam * synth.interior(JV))
+    for x in (one, got):
+        a = np.sum(x * v)
+        assert abs(a - b) <= 1e-12 * np.sum(np.abs(x * v)), (a, b)
