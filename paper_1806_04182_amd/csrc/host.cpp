@@ -521,8 +521,14 @@ int build_tiles(const Level& lev, const int shape[3], int margin, TileList& tl, 
 // planes) and 512^3 (whole 512-plane columns, no chunk-boundary re-reads));
 // so do levels of at least 2^18 points whose patches fill the columns to 60%
 // (stage on one periodic patch, point-wise against marching: 64^3 9.3 and 7.3
-// us, 80^3 (62% full) 17.7 and 16.1, 96^3 23.1 and 21.6, 120^3 44 and 29; at
-// 48^3, where the columns are 75% full, 7.3 and 7.0, and at 32^3 4.2 and 6.3);
+// us, 96^3 23.1 and 20, 120^3 44 and 32; at 48^3, where the columns are 75%
+// full, 7.3 and 7.0, and at 32^3 4.2 and 6.3), in the shortest chunks that make
+// no more than 512 workgroups, which is the fastest of 2 to 16 planes on nearly
+// all such levels (127^3 36.4 us with 8 planes, 45.8 with 7, whose 608
+// workgroups leave a third one to some compute units; 60 x 120 x 220 31.2 with
+// 7, 41.2 with 6; 100 x 60 x 50 10.1 with 2, 10.9 with 4); levels of so many
+// columns that this takes more than 8 planes stay at about 512 workgroups of
+// full columns (27 patches of 40^3: 43 us with 6 planes, 47 with 14);
 // other levels use one thread per point.  MHD: the z chunk that minimises
 // rounds of 256 workgroups (one per compute unit; two for WENO3, whose kernel
 // fits two) times the planes of a chunk and its lead-in (two z reconstructions, 0.7 of a plane; flux splitting: one
@@ -537,15 +543,25 @@ void default_tile(const SysParams& sp, const Level& lev, int td[3])
         level_points += (int64_t)pd.n[0] * pd.n[1] * pd.n[2];
         column_points += round_up(pd.n[0], MOL_WAVE_WX) * round_up(pd.n[1], MOL_WAVE_WY) * pd.n[2];
     }
+    // workgroups of wx x wy columns and zc planes
+    auto workgroups = [&](int wx, int wy, int zc) {
+        int64_t n = 0;
+        for (const PatchDev& pd : lev.pd)
+            n += round_up(pd.n[0], wx) / wx * (round_up(pd.n[1], wy) / wy) * (round_up(pd.n[2], zc) / zc);
+        return n;
+    };
     switch (system) {
     case MOL_WAVE:
-        if (level_points >= (int64_t(1) << 21) ||
-            (level_points >= (int64_t(1) << 18) && 10 * level_points >= 6 * column_points)) {
+        if (level_points >= (int64_t(1) << 21)) {
             td[0] = MOL_WAVE_WX;
             td[1] = MOL_WAVE_WY;
             td[2] = (int)std::max<int64_t>(
-                level_points >= (int64_t(1) << 21) ? 4 : 2,
-                std::min<int64_t>(MOL_WAVE_ZMAX, level_points / (MOL_WAVE_WX * MOL_WAVE_WY * 512)));
+                4, std::min<int64_t>(MOL_WAVE_ZMAX, level_points / (MOL_WAVE_WX * MOL_WAVE_WY * 512)));
+        } else if (level_points >= (int64_t(1) << 18) && 10 * level_points >= 6 * column_points) {
+            td[0] = MOL_WAVE_WX;
+            td[1] = MOL_WAVE_WY;
+            for (td[2] = 2; td[2] < 9 && workgroups(MOL_WAVE_WX, MOL_WAVE_WY, td[2]) > 512;) ++td[2];
+            if (td[2] == 9) td[2] = (int)std::max<int64_t>(2, level_points / (MOL_WAVE_WX * MOL_WAVE_WY * 512));
         } else {
             td[0] = 32;
             td[1] = 4;
@@ -559,9 +575,7 @@ void default_tile(const SysParams& sp, const Level& lev, int td[3])
         const int slots = !split && sp.mhd_recon == MOL_RECON_WENO3 ? 512 : 256;
         double best = 0.0;
         for (int zc = 1; zc <= 32; ++zc) {
-            int64_t tiles = 0;
-            for (const PatchDev& pd : lev.pd)
-                tiles += round_up(pd.n[0], wx) / wx * (round_up(pd.n[1], wy) / wy) * (round_up(pd.n[2], zc) / zc);
+            const int64_t tiles = workgroups(wx, wy, zc);
             const double cost = (double)((tiles + slots - 1) / slots) * (zc + (split ? 0.35 : 0.7));
             if (zc == 1 || cost < best) {
                 best = cost;
