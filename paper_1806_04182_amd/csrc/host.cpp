@@ -531,10 +531,16 @@ int build_tiles(const Level& lev, const int shape[3], int margin, TileList& tl, 
 // full columns (27 patches of 40^3: 43 us with 6 planes, 47 with 14);
 // other levels use one thread per point.  MHD: the z chunk that minimises
 // rounds of 256 workgroups (one per compute unit; two for WENO3, whose kernel
-// fits two) times the planes of a chunk and its lead-in (two z reconstructions, 0.7 of a plane; flux splitting: one
-// z flux, 0.35).  Measured at 128^3 (WENO5-Z, LLF) 393 us with chunks of 8
-// (cost 43), 424 with 4 (47), 445 with 16 (50), 487 with 2 (54); at 32^3 24 us
-// with 2 and 40 with 4.
+// fits two) times the planes of a chunk and its lead-in (two z
+// reconstructions, 0.7 of a plane; flux splitting: one z flux, whose loads the
+// first plane shares, 0.1).  Measured at 128^3 (WENO5-Z, LLF) 393 us with chunks
+// of 8 (cost 43), 424 with 4 (47), 445 with 16 (50), 487 with 2 (54); at 32^3 24
+// us with 2 and 40 with 4.  Flux splitting takes chunks of 4 within 2.5% of the
+// lowest cost, since many rounds even out tiles of few columns (WENO3, 27
+// patches of 32^3 571 us with 4, 608 with 32; 8 of 36^3 196 and 204 with 12; 8
+// of 48^3 432 and 444 with 24), except for one chunk per patch of up to 24
+// planes (WENO5-Z, 64 patches of 16^3 484 with 4, 429 with 16; 64 of 24^3 598
+// and 576).
 void default_tile(const SysParams& sp, const Level& lev, int td[3])
 {
     const int system = sp.system;
@@ -573,15 +579,19 @@ void default_tile(const SysParams& sp, const Level& lev, int td[3])
         const bool split = !mhd_cell_columns(sp);
         const int wx = split ? 15 : MHD_CX, wy = split ? 15 : MHD_CY;
         const int slots = !split && sp.mhd_recon == MOL_RECON_WENO3 ? 512 : 256;
-        double best = 0.0;
+        double best = 0.0, four = 0.0;
         for (int zc = 1; zc <= 32; ++zc) {
-            const int64_t tiles = workgroups(wx, wy, zc);
-            const double cost = (double)((tiles + slots - 1) / slots) * (zc + (split ? 0.35 : 0.7));
+            const int64_t rounds = (workgroups(wx, wy, zc) + slots - 1) / slots;
+            const double cost = (double)rounds * (zc + (split ? 0.1 : 0.7));
             if (zc == 1 || cost < best) {
                 best = cost;
                 td[2] = zc;
             }
+            if (zc == 4) four = cost;
         }
+        int nz = 0;
+        for (const PatchDev& pd : lev.pd) nz = std::max(nz, pd.n[2]);
+        if (split && four <= 1.025 * best && !(td[2] >= nz && nz <= 24)) td[2] = 4;
         td[0] = td[1] = 15;  // the shape's name; see MHD_CX
         break;
     }
