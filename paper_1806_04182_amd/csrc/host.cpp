@@ -189,6 +189,7 @@ struct TileList {
     std::vector<int> by_patch;  // start of each patch's tiles, then the total
     std::vector<int> count;     // tiles of each patch
     int order = 0;              // patch order in the launch: 0 as given, 1 largest first
+    bool cells = false;         // MHD stage tiles of the cell kernel's columns
 };
 
 }  // namespace
@@ -457,11 +458,32 @@ struct FineCells {
     }
 };
 
-// whether the level's stage kernel is the MHD one whose workgroups own MHD_CX x
-// MHD_CY columns (LLF and HLL; flux splitting owns 15 x 15)
-bool mhd_cell_columns(const SysParams& sp)
+// workgroups of wx x wy columns and zc planes that cover a level's patches
+int64_t column_tiles(const Level& lev, int wx, int wy, int zc)
 {
-    return (sp.system == MOL_MHD || sp.system == MOL_MHD_GLM) && sp.mhd_flux != MOL_FLUX_SPLIT;
+    int64_t n = 0;
+    for (const PatchDev& pd : lev.pd)
+        n += round_up(pd.n[0], wx) / wx * (round_up(pd.n[1], wy) / wy) * (round_up(pd.n[2], zc) / zc);
+    return n;
+}
+
+// Whether a level's stage kernel is the MHD cell kernel, whose workgroups own
+// MHD_CX x MHD_CY columns: for LLF and HLL, unless the level fills the chip and
+// that takes 1.8 times the workgroups of 15 x 15 columns, as on patches 15
+// columns wide (cell against interface kernel, 125 patches of 15^3: WENO5-Z 147
+// and 111 us, WENO5-JS 143 and 108, WENO3 105 and 87, nine fields 141 and 103,
+// but with WENO5 171 and 200; 64 of them: WENO5-Z 83 and 75, WENO3 56 and 60; eight:
+// 17.5 and 19.5, 13.2 and 15.0; at 1.5 times, 64 patches of 30^3, 454 and 473).  A
+// general exponent of WENO5-Z stays with the cell kernel, which takes half the
+// powers (and rounds them in its own way, where the two kernels otherwise
+// agree bit for bit).
+bool mhd_cell_columns(const SysParams& sp, const Level& lev)
+{
+    if ((sp.system != MOL_MHD && sp.system != MOL_MHD_GLM) || sp.mhd_flux == MOL_FLUX_SPLIT) return false;
+    const bool weno3 = sp.mhd_recon == MOL_RECON_WENO3, glm = sp.system == MOL_MHD_GLM;
+    if ((glm && !weno3) || (sp.mhd_recon == MOL_RECON_WENO5Z && sp.weno_q != 2.0)) return true;
+    const int64_t planes = column_tiles(lev, MHD_CX, MHD_CY, 1);
+    return planes <= (weno3 && !glm ? 2048 : 512) || 20 * planes < (glm ? 29 : 36) * column_tiles(lev, 15, 15, 1);
 }
 
 // tiles of td[0] x td[1] x td[2] points over every patch (grown by margin),
@@ -471,10 +493,10 @@ bool mhd_cell_columns(const SysParams& sp)
 int build_tiles(const Level& lev, const int shape[3], int margin, TileList& tl, Arena* A, int order = 0,
                 const SysParams* stage = nullptr)
 {
-    // the points a tile covers: the launch shape, except for the MHD kernel
-    // whose workgroups own MHD_CX x MHD_CY columns
+    // the points a tile covers: the launch shape, except for the MHD cell kernel
     int td[3] = {shape[0], shape[1], shape[2]};
-    if (stage && mhd_cell_columns(*stage)) {
+    tl.cells = stage && mhd_cell_columns(*stage, lev);
+    if (tl.cells) {
         td[0] = MHD_CX;
         td[1] = MHD_CY;
     }
@@ -532,15 +554,17 @@ int build_tiles(const Level& lev, const int shape[3], int margin, TileList& tl, 
 // other levels use one thread per point.  MHD: the z chunk that minimises
 // rounds of 256 workgroups (one per compute unit; two for WENO3, whose kernel
 // fits two) times the planes of a chunk and its lead-in (two z
-// reconstructions, 0.7 of a plane; flux splitting: one z flux, whose loads the
-// first plane shares, 0.1).  Measured at 128^3 (WENO5-Z, LLF) 393 us with chunks
+// reconstructions, 0.7 of a plane; interface kernel: one z flux, whose loads
+// the first plane shares, 0.1).  Measured at 128^3 (WENO5-Z, LLF) 393 us with chunks
 // of 8 (cost 43), 424 with 4 (47), 445 with 16 (50), 487 with 2 (54); at 32^3 24
 // us with 2 and 40 with 4.  Flux splitting takes chunks of 4 within 2.5% of the
 // lowest cost, since many rounds even out tiles of few columns (WENO3, 27
 // patches of 32^3 571 us with 4, 608 with 32; 8 of 36^3 196 and 204 with 12; 8
 // of 48^3 432 and 444 with 24), except for one chunk per patch of up to 24
 // planes (WENO5-Z, 64 patches of 16^3 484 with 4, 429 with 16; 64 of 24^3 598
-// and 576).
+// and 576).  LLF and HLL on the interface kernel gain from a second workgroup
+// on a compute unit: a round without a second counts 1.5 (nine fields WENO3, 64
+// patches of 30^3, 579 us in one round of 30 planes, 398 in two of 15).
 void default_tile(const SysParams& sp, const Level& lev, int td[3])
 {
     const int system = sp.system;
@@ -549,13 +573,6 @@ void default_tile(const SysParams& sp, const Level& lev, int td[3])
         level_points += (int64_t)pd.n[0] * pd.n[1] * pd.n[2];
         column_points += round_up(pd.n[0], MOL_WAVE_WX) * round_up(pd.n[1], MOL_WAVE_WY) * pd.n[2];
     }
-    // workgroups of wx x wy columns and zc planes
-    auto workgroups = [&](int wx, int wy, int zc) {
-        int64_t n = 0;
-        for (const PatchDev& pd : lev.pd)
-            n += round_up(pd.n[0], wx) / wx * (round_up(pd.n[1], wy) / wy) * (round_up(pd.n[2], zc) / zc);
-        return n;
-    };
     switch (system) {
     case MOL_WAVE:
         if (level_points >= (int64_t(1) << 21)) {
@@ -566,7 +583,7 @@ void default_tile(const SysParams& sp, const Level& lev, int td[3])
         } else if (level_points >= (int64_t(1) << 18) && 10 * level_points >= 6 * column_points) {
             td[0] = MOL_WAVE_WX;
             td[1] = MOL_WAVE_WY;
-            for (td[2] = 2; td[2] < 9 && workgroups(MOL_WAVE_WX, MOL_WAVE_WY, td[2]) > 512;) ++td[2];
+            for (td[2] = 2; td[2] < 9 && column_tiles(lev, MOL_WAVE_WX, MOL_WAVE_WY, td[2]) > 512;) ++td[2];
             if (td[2] == 9) td[2] = (int)std::max<int64_t>(2, level_points / (MOL_WAVE_WX * MOL_WAVE_WY * 512));
         } else {
             td[0] = 32;
@@ -576,13 +593,14 @@ void default_tile(const SysParams& sp, const Level& lev, int td[3])
         break;
     case MOL_MHD:
     case MOL_MHD_GLM: {
-        const bool split = !mhd_cell_columns(sp);
-        const int wx = split ? 15 : MHD_CX, wy = split ? 15 : MHD_CY;
-        const int slots = !split && sp.mhd_recon == MOL_RECON_WENO3 ? 512 : 256;
+        const bool cells = mhd_cell_columns(sp, lev), split = sp.mhd_flux == MOL_FLUX_SPLIT;
+        const int wx = cells ? MHD_CX : 15, wy = cells ? MHD_CY : 15;
+        const int slots = cells && sp.mhd_recon == MOL_RECON_WENO3 ? 512 : 256;
         double best = 0.0, four = 0.0;
         for (int zc = 1; zc <= 32; ++zc) {
-            const int64_t rounds = (workgroups(wx, wy, zc) + slots - 1) / slots;
-            const double cost = (double)rounds * (zc + (split ? 0.1 : 0.7));
+            const int64_t rounds = (column_tiles(lev, wx, wy, zc) + slots - 1) / slots;
+            const double single = !cells && !split && rounds % 2 ? 0.5 : 0.0;
+            const double cost = (rounds + single) * (zc + (cells ? 0.7 : 0.1));
             if (zc == 1 || cost < best) {
                 best = cost;
                 td[2] = zc;
@@ -628,9 +646,9 @@ void reuse_level(mol_patchset* ps, const mol_patchset* prev, int l)
     lev.rst_by_patch = o.rst_by_patch;
     TileList* mine[6] = {&lev.tiles, &lev.gtiles, &lev.ntiles, &lev.ptiles, &lev.wtiles, &lev.ctiles};
     const TileList* theirs[6] = {&o.tiles, &o.gtiles, &o.ntiles, &o.ptiles, &o.wtiles, &o.ctiles};
-    // MHD with another kind of flux: prev's stage tiles cover other columns
-    // than this system's kernel owns
-    const bool own = mhd_cell_columns(ps->sp) != mhd_cell_columns(prev->sp);
+    // MHD with another flux or reconstruction: prev's stage tiles may cover
+    // other columns than this system's kernel owns
+    const bool own = mhd_cell_columns(ps->sp, lev) != o.tiles.cells;
     if (own) {
         int td[3];
         default_tile(ps->sp, lev, td);
@@ -641,6 +659,7 @@ void reuse_level(mol_patchset* ps, const mol_patchset* prev, int l)
         mine[i]->by_patch = theirs[i]->by_patch;
         mine[i]->count = theirs[i]->count;
         mine[i]->order = theirs[i]->order;
+        mine[i]->cells = theirs[i]->cells;
         mine[i]->dev.adopt(theirs[i]->dev, A);
     }
     lev.wofs.adopt(o.wofs, A);
@@ -1118,6 +1137,7 @@ int stage_impl(mol_patchset* ps, int level, int mode, int stage, double dt, cons
     a.stream = lev.nelems * (int64_t)sizeof(double) >= (int64_t(128) << 20);
     a.wrap = wrap ? 1 : 0;
     a.swap = swap ? 1 : 0;
+    a.mhd_cells = lev.tiles.cells ? 1 : 0;
     a.images = images ? 1 : 0;
     if (!plain) {
         a.tiles = lev.tiles.dev.p;

@@ -89,7 +89,7 @@ __device__ __forceinline__ double weno3(double v1, double v2, double v3, double 
 }
 
 enum { REC_W5Z = 0, REC_W5JS = 1, REC_W3 = 2 };
-enum { RS_LLF = 0, RS_HLL = 1 };
+enum { RS_LLF = 0, RS_HLL = 1, RS_SPLIT = 2 };
 
 // reconstructed value at the interface to the right of v2 from the left
 template <int REC, bool Q2>
@@ -137,7 +137,7 @@ __device__ __forceinline__ void flux(const double U[8], int d, double gam, doubl
 // Interface flux by flux splitting between cells 2 and 3 of a six-cell line;
 // get(f, m) returns cell m (0..5) of field f.
 template <int NF, int REC, bool Q2, class Get>
-__device__ __forceinline__ void riemann6(Get get, int d, const MhdConst& C, double Fh[NF])
+__device__ __forceinline__ void split_flux(Get get, int d, const MhdConst& C, double Fh[NF])
 {
     // (F +- alpha U)/2 of the six cells, alpha the largest signal speed
     // among them; left-biased reconstruction of the + part around cell 2,
@@ -252,14 +252,38 @@ __device__ __forceinline__ void interface_flux(const double UL[NF], const double
         }
         SL = fmin(SL, 0.0);
         SR = fmax(SR, 0.0);
-        const double id = 1.0 / (SR - SL), SRL = SR * SL;
+        // (an explicit last fma: neither kernel fuses the flux into a difference)
+        const double id = 1.0 / (SR - SL), aL = SR * id, aR = -SL * id, aU = SR * SL * id;
 #pragma unroll
-        for (int f = 0; f < NF; ++f) Fh[f] = (SR * FL[f] - SL * FR[f] + SRL * (UR[f] - UL[f])) * id;
+        for (int f = 0; f < NF; ++f) Fh[f] = fma(aL, FL[f], fma(aR, FR[f], aU * (UR[f] - UL[f])));
     } else {
         double S = fmax(fabs(vL) + cL, fabs(vR) + cR);
         if constexpr (NF == 9) S = fmax(S, C.ch);
 #pragma unroll
-        for (int f = 0; f < NF; ++f) Fh[f] = 0.5 * (FL[f] + FR[f] - S * (UR[f] - UL[f]));
+        for (int f = 0; f < 8; ++f) Fh[f] = 0.5 * (FL[f] + FR[f] - S * (UR[f] - UL[f]));
+        // (one rounding order: of ch2 U^L + ch2 U^R either product could be fused)
+        if constexpr (NF == 9) Fh[8] = 0.5 * fma(-S, UR[8] - UL[8], C.ch2 * (UL[5 + d] + UR[5 + d]));
+    }
+}
+
+// Interface flux between cells 2 and 3 of a six-cell line: get(f, m) is cell m
+// of field f.  LLF and HLL take the states that cell_states gives each of the
+// two cells, so that both kernels below give the same bits.
+template <int NF, int REC, int RS, bool Q2, class Get>
+__device__ __forceinline__ void face_flux(Get get, int d, const MhdConst& C, double Fh[NF])
+{
+    if constexpr (RS == RS_SPLIT) {
+        split_flux<NF, REC, Q2>(get, d, C, Fh);
+    } else {
+        const double es = REC == REC_W3 ? C.eps : 4.0 * C.eps;
+        double UL[NF], UR[NF], unused;
+#pragma unroll
+        for (int f = 0; f < NF; ++f) {
+            const double c0 = get(f, 0), c1 = get(f, 1), c2 = get(f, 2), c3 = get(f, 3), c4 = get(f, 4), c5 = get(f, 5);
+            cell_states<REC, Q2>(c0, c1, c2, c3, c4, es, C.q, UL[f], unused);
+            cell_states<REC, Q2>(c1, c2, c3, c4, c5, es, C.q, unused, UR[f]);
+        }
+        interface_flux<NF, RS>(UL, UR, d, C, Fh);
     }
 }
 
@@ -453,8 +477,11 @@ __global__ __launch_bounds__(256, REC == REC_W3 ? 2 : 1) void mhd_cells_kernel(S
     }
 }
 
-// Flux splitting (its reconstruction depends on the interface, so nothing is
-// shared between the states of a cell).
+// Interface by interface: flux splitting (its reconstruction depends on the
+// interface, so nothing is shared between the states of a cell), and LLF and HLL
+// on levels whose patches its 15 x 15 columns fit so much better than 14 x 16
+// that twice the reconstructions cost less (125 patches of 15^3, where the cell
+// kernel needs two tiles per patch: WENO5-Z 147 -> 111 us).
 // One workgroup of 16 x 16 threads owns a tile of 15 x 15 columns and marches
 // along z over ZC planes.  Per plane: the plane (with a 3-cell halo in x and
 // y) is staged in LDS; thread (tx, ty) computes the x-interface flux to the
@@ -469,8 +496,8 @@ constexpr int MB = MT + 1;       // threads per tile edge
 constexpr int MH = MT + 6;       // plane width with halo
 constexpr int MP = MH + 1;       // LDS row pitch
 
-template <int NF, int REC, bool Q2>
-__global__ __launch_bounds__(MB * MB) void mhd_split_kernel(StageArgs a, MhdConst C, int zc)
+template <int NF, int REC, int RS, bool Q2>
+__global__ __launch_bounds__(MB * MB) void mhd_faces_kernel(StageArgs a, MhdConst C, int zc)
 {
     __shared__ double pl[NF][MH][MP];
     __shared__ double fx[NF][MT][MB];
@@ -487,6 +514,7 @@ __global__ __launch_bounds__(MB * MB) void mhd_split_kernel(StageArgs a, MhdCons
     const int64_t colbase = P.off + (int64_t)(y0 + ty + G) * P.pitch_y + (x0 + tx + G);
     const double* __restrict__ Us = a.Us;
 
+    [[maybe_unused]] const StageCoef sc = stage_coef(a);
     double w[NF][6];  // cells k-2 .. k+3 of the own column
     double Fm[NF];    // z-flux below the current plane
     if (col) {
@@ -499,7 +527,7 @@ __global__ __launch_bounds__(MB * MB) void mhd_split_kernel(StageArgs a, MhdCons
         for (int f = 0; f < NF; ++f)
 #pragma unroll
             for (int m = 0; m < 6; ++m) w[f][m] = c7[f][m + 1];
-        riemann6<NF, REC, Q2>([&](int f, int m) { return c7[f][m]; }, 2, C, Fm);
+        face_flux<NF, REC, RS, Q2>([&](int f, int m) { return c7[f][m]; }, 2, C, Fm);
     }
     for (int k = z0; k < z1; ++k) {
         // stage plane k with its x/y halo
@@ -512,17 +540,17 @@ __global__ __launch_bounds__(MB * MB) void mhd_split_kernel(StageArgs a, MhdCons
         __syncthreads();
         // x-interface to the left of column (tx, ty): cells tx-3 .. tx+2 of row ty
         double Fp[NF];
-        if (col) riemann6<NF, REC, Q2>([&](int f, int m) { return w[f][m]; }, 2, C, Fp);
+        if (col) face_flux<NF, REC, RS, Q2>([&](int f, int m) { return w[f][m]; }, 2, C, Fp);
         if (ty < MT && x0 + tx <= P.n[0] && y0 + ty < P.n[1]) {
             double F[NF];
-            riemann6<NF, REC, Q2>([&](int f, int m) { return pl[f][ty + G][tx + m]; }, 0, C, F);
+            face_flux<NF, REC, RS, Q2>([&](int f, int m) { return pl[f][ty + G][tx + m]; }, 0, C, F);
 #pragma unroll
             for (int f = 0; f < NF; ++f) fx[f][ty][tx] = F[f];
         }
         // y-interface below column (tx, ty)
         if (tx < MT && y0 + ty <= P.n[1] && x0 + tx < P.n[0]) {
             double F[NF];
-            riemann6<NF, REC, Q2>([&](int f, int m) { return pl[f][ty + m][tx + G]; }, 1, C, F);
+            face_flux<NF, REC, RS, Q2>([&](int f, int m) { return pl[f][ty + m][tx + G]; }, 1, C, F);
 #pragma unroll
             for (int f = 0; f < NF; ++f) fy[f][ty][tx] = F[f];
         }
@@ -531,11 +559,16 @@ __global__ __launch_bounds__(MB * MB) void mhd_split_kernel(StageArgs a, MhdCons
             const int64_t cidx = colbase + (int64_t)(k + G) * sz;
 #pragma unroll
             for (int f = 0; f < NF; ++f) {
-                const double div = (fx[f][ty][tx + 1] - fx[f][ty][tx]) + (fy[f][ty + 1][tx] - fy[f][ty][tx]) +
-                                   (Fp[f] - Fm[f]);
+                const double dx = fx[f][ty][tx + 1] - fx[f][ty][tx], dy = fy[f][ty + 1][tx] - fy[f][ty][tx];
+                // (LLF, HLL: in the cell kernel's order)
+                const double div = RS == RS_SPLIT ? dx + dy + (Fp[f] - Fm[f]) : (Fp[f] - Fm[f]) + dx + dy;
                 // psi: the damping source at the cell (w[8][2] is plane k of the column)
                 const double rhs = f == 8 ? -div * C.ih - C.kpsi * w[f][2] : -div * C.ih;
-                stage_store(a, cidx + f * fs, rhs);
+                const int64_t i = cidx + f * fs;
+                if constexpr (RS == RS_SPLIT)
+                    stage_store(a, i, rhs);
+                else
+                    a.out[i] = stage_update(a, sc, i, rhs, sc.pun[i], sc.pw[i]);
             }
             if (k + 1 < z1) {
 #pragma unroll
@@ -551,32 +584,26 @@ __global__ __launch_bounds__(MB * MB) void mhd_split_kernel(StageArgs a, MhdCons
     }
 }
 
+template <int NF, int REC, bool Q2>
+void launch(const SysParams& sp, const StageArgs& a, const MhdConst& C, int zc, hipStream_t s)
+{
+    auto go = [&](auto kernel) { kernel<<<a.ntiles, dim3(16, 16, 1), 0, s>>>(a, C, zc); };
+    const bool hll = sp.mhd_flux == MOL_FLUX_HLL;
+    if (sp.mhd_flux == MOL_FLUX_SPLIT)
+        go(mhd_faces_kernel<NF, REC, RS_SPLIT, Q2>);
+    else if (a.mhd_cells)
+        hll ? go(mhd_cells_kernel<NF, REC, RS_HLL, Q2>) : go(mhd_cells_kernel<NF, REC, RS_LLF, Q2>);
+    else if constexpr ((NF == 8 || REC == REC_W3) && Q2)
+        hll ? go(mhd_faces_kernel<NF, REC, RS_HLL, Q2>) : go(mhd_faces_kernel<NF, REC, RS_LLF, Q2>);
+}
+
 template <int NF>
 hipError_t dispatch(const SysParams& sp, const StageArgs& a, const MhdConst& C, int zc, hipStream_t s)
 {
-    const dim3 g(a.ntiles), b(16, 16, 1);
-    const bool hll = sp.mhd_flux == MOL_FLUX_HLL;
-    auto go = [&](auto kernel) { kernel<<<g, b, 0, s>>>(a, C, zc); };
-    if (sp.mhd_flux == MOL_FLUX_SPLIT) {
-        switch (sp.mhd_recon) {
-        case MOL_RECON_WENO3: go(mhd_split_kernel<NF, REC_W3, true>); break;
-        case MOL_RECON_WENO5JS: go(mhd_split_kernel<NF, REC_W5JS, true>); break;
-        default: C.q == 2.0 ? go(mhd_split_kernel<NF, REC_W5Z, true>) : go(mhd_split_kernel<NF, REC_W5Z, false>);
-        }
-        return hipGetLastError();
-    }
     switch (sp.mhd_recon) {
-    case MOL_RECON_WENO3:
-        hll ? go(mhd_cells_kernel<NF, REC_W3, RS_HLL, true>) : go(mhd_cells_kernel<NF, REC_W3, RS_LLF, true>);
-        break;
-    case MOL_RECON_WENO5JS:
-        hll ? go(mhd_cells_kernel<NF, REC_W5JS, RS_HLL, true>) : go(mhd_cells_kernel<NF, REC_W5JS, RS_LLF, true>);
-        break;
-    default:
-        if (C.q == 2.0)
-            hll ? go(mhd_cells_kernel<NF, REC_W5Z, RS_HLL, true>) : go(mhd_cells_kernel<NF, REC_W5Z, RS_LLF, true>);
-        else
-            hll ? go(mhd_cells_kernel<NF, REC_W5Z, RS_HLL, false>) : go(mhd_cells_kernel<NF, REC_W5Z, RS_LLF, false>);
+    case MOL_RECON_WENO3: launch<NF, REC_W3, true>(sp, a, C, zc, s); break;
+    case MOL_RECON_WENO5JS: launch<NF, REC_W5JS, true>(sp, a, C, zc, s); break;
+    default: C.q == 2.0 ? launch<NF, REC_W5Z, true>(sp, a, C, zc, s) : launch<NF, REC_W5Z, false>(sp, a, C, zc, s);
     }
     return hipGetLastError();
 }

@@ -26,8 +26,8 @@ constexpr int G = MOL_GHOST;
 #define MOL_CCZ4_TY 8
 #define MOL_CCZ4_TZ 4
 #endif
-// columns per workgroup of the MHD kernel for the LLF and HLL fluxes (the
-// launch shape 15 x 15 x z names its z chunk; flux splitting keeps 15 x 15)
+// columns per workgroup of the MHD cell kernel (LLF and HLL; the launch shape
+// 15 x 15 x z names its z chunk; the interface kernel owns 15 x 15)
 constexpr int MHD_CX = 14, MHD_CY = 16;
 // minimum waves per SIMD of the CCZ4 kernel
 #ifndef MOL_CCZ4_WAVES
@@ -174,6 +174,9 @@ struct StageArgs {
     // stencils are symmetric, so d_t (Pi, phi) of the transpose is the forward
     // right-hand side)
     int swap;
+    // 1 when the tiles of an MHD level cover MHD_CX x MHD_CY columns (the cell
+    // kernel), 0 when they cover 15 x 15 (the interface kernel)
+    int mhd_cells;
     // 1 when the driver steps a CCZ4 level that is one periodic patch of at
     // least 2G points per axis: the stage kernel also writes its output at
     // the periodic ghost images of every point within G of a face (faces,

@@ -478,3 +478,45 @@ def test_mhd_weights_keep_their_range(recon, scale):
         assert np.count_nonzero(~np.isfinite(ref)) == 0 and np.count_nonzero(~np.isfinite(got)) == 0
         e = parity_err(got, ref)
         assert np.all(e <= TOL), e
+
+
+@pytest.mark.parametrize("system,recon,q", [(M.MOL_MHD, M.MOL_RECON_WENO5Z, 2.0), (M.MOL_MHD, M.MOL_RECON_WENO5Z, 1.5),
+                                            (M.MOL_MHD, M.MOL_RECON_WENO5JS, 2.0), (M.MOL_MHD, M.MOL_RECON_WENO3, 2.0),
+                                            (M.MOL_MHD_GLM, M.MOL_RECON_WENO3, 2.0),
+                                            (M.MOL_MHD_GLM, M.MOL_RECON_WENO5Z, 1.5)])
+@pytest.mark.parametrize("ny,tiles", [(15, 4), (29, 8)])
+def test_mhd_cell_and_interface_kernels_agree(ny, tiles, system, recon, q):
+    """A level that fills the chip with patches 15 columns wide takes the
+    interface kernel (15 x 15 columns) for LLF and HLL, the same box in one patch
+    of 30 columns the cell kernel (14 x 16; with a general WENO5-Z exponent both
+    do): one SSP-RK3 and one RK4 step bit for bit, and against the oracle."""
+    torch = _torch()
+    # a few planes more than the interface kernel needs (512 or 2048 tiles of one plane)
+    nz = (2048 if recon == M.MOL_RECON_WENO3 and system == M.MOL_MHD else 512) // tiles + 3
+    n = (30, ny, nz)
+    dx = 1.0 / 30
+    nf = 9 if system == M.MOL_MHD_GLM else 8
+    st0 = synth.mhd_ot_like(n, seed=6)
+    if nf == 9:
+        st0 = np.concatenate([st0, 1e-2 * st0[1:2]])
+    boxes = {1: [((0, 0, 0), (29, ny - 1, nz - 1))],
+             2: [((0, 0, 0), (14, ny - 1, nz - 1)), ((15, 0, 0), (29, ny - 1, nz - 1))]}
+    osys = O.MHD_GLM if nf == 9 else O.MHD
+    for flux in (M.MOL_FLUX_LLF, M.MOL_FLUX_HLL):
+        print("mhd kernels", n, system, recon, q, flux, flush=True)
+        sysd = M.System(system, sigma=0.0, weno_q=q, mhd_recon=recon, mhd_flux=flux, mhd_ch=1.3, mhd_kpsi=0.7)
+        prm = O.params(sigma=0.0, weno_q=q, mhd_recon=float(recon), mhd_riemann=float(flux), mhd_ch=1.3, mhd_kpsi=0.7)
+        for mode, scheme in ((M.MOL_ADV_SSPRK3, O.SSPRK3), (0, O.RK4)):
+            out = []
+            for b in boxes.values():
+                ps = M.Patchset(M.Hierarchy(n, (0.0, 0.0, 0.0), dx, [(1, b)]), sysd)
+                st = ps.alloc_states()
+                parts = [synth.embed(np.ascontiguousarray(st0[:, :, :, lo[0]:hi[0] + 1])) for lo, hi in b]
+                st[0]["U"].copy_(torch.from_numpy(ps.pack(0, parts)))
+                ps.advance(st, 0.1 * dx, M.MOL_BATCHED | mode)
+                torch.cuda.synchronize()
+                out.append(np.concatenate([synth.interior(a) for a in ps.unpack(0, st[0]["U"])], axis=3))
+            assert np.array_equal(out[0], out[1])
+            ref = _oracle_steps(osys, scheme, synth.embed(st0), dx, 0.1 * dx, 1, prm)
+            e = parity_err(out[1], synth.interior(ref))
+            assert np.all(e <= TOL), e
