@@ -10,7 +10,6 @@
 #include <algorithm>
 #include <array>
 #include <limits>
-#include <map>
 #include <mutex>
 #include <tuple>
 #include <cmath>
@@ -19,6 +18,7 @@
 #include <cstring>
 #include <new>
 #include <string>
+#include <unordered_map>
 #include <vector>
 
 #include "molamr_int.h"
@@ -278,16 +278,14 @@ struct mol_patchset {
 struct mol_regrid {
     mol_patchset* pn = nullptr;
     const mol_patchset* po = nullptr;
-    DevArr<GhostCopy> copy[MOL_MAX_LEVELS];   // new <- old at the same level
+    DevArr<GhostCopy> copy[MOL_MAX_LEVELS];       // new <- old at the same level
+    Arena arena;                                  // of the tables below
     DevArr<ProlongBrick> bricks[MOL_MAX_LEVELS];  // new points interpolated from the new parent
     DevArr<uint32_t> rows[MOL_MAX_LEVELS];
     ~mol_regrid()
     {
-        for (int l = 0; l < MOL_MAX_LEVELS; ++l) {
-            copy[l].release();
-            bricks[l].release();
-            rows[l].release();
-        }
+        for (auto& c : copy) c.release();
+        arena.release();
     }
 };
 
@@ -369,20 +367,27 @@ int floor_div(int a, int b) { return a >= 0 ? a / b : -((-a + b - 1) / b); }
 // node i0 and i0's wrapped position, and the present points m.
 struct FineCells {
     struct Cell {
-        int key[3], q0, cw[3];
+        std::array<int, 3> key;
+        int q0, cw[3];
         uint64_t mask;
     };
     std::vector<Cell> cells;
-    std::map<std::array<int, 3>, size_t> index;
+    struct Hash {
+        size_t operator()(const std::array<int, 3>& k) const
+        {
+            return ((size_t)k[2] * 0x9E3779B97F4A7C15u + (size_t)k[1]) * 0xBF58476D1CE4E5B9u + (size_t)k[0];
+        }
+    };
+    std::unordered_map<std::array<int, 3>, uint32_t, Hash> index;
+    size_t last = 0;  // the cell of the last point (points come in rows)
     void add(const int g[3], const int m[3], int R, int q0, const int cw[3])
     {
         const std::array<int, 3> key = {floor_div(g[0], R), floor_div(g[1], R), floor_div(g[2], R)};
-        auto it = index.find(key);
-        if (it == index.end()) {
-            it = index.emplace(key, cells.size()).first;
-            cells.push_back(Cell{{key[0], key[1], key[2]}, q0, {cw[0], cw[1], cw[2]}, 0});
+        if (cells.empty() || key != cells[last].key) {
+            last = index.try_emplace(key, (uint32_t)cells.size()).first->second;
+            if (last == cells.size()) cells.push_back(Cell{key, q0, {cw[0], cw[1], cw[2]}, 0});
         }
-        cells[it->second].mask |= uint64_t(1) << ((m[2] * R + m[1]) * R + m[0]);
+        cells[last].mask |= uint64_t(1) << ((m[2] * R + m[1]) * R + m[0]);
     }
     // append the cells' bricks: cells of one parent patch and one wrap offset
     // in blocks aligned at the lowest cell, each cut to the bounding box of
@@ -399,38 +404,49 @@ struct FineCells {
                 lo[d] = std::min(lo[d], c.key[d]);
                 hi[d] = std::max(hi[d], c.key[d]);
             }
-        std::map<std::array<int, 8>, std::vector<size_t>> blocks;
+        // parent patches and wrap offsets that occur (few), and each cell's block:
+        // place among them, block coordinates (z slowest) and slab axis
+        std::vector<std::array<int, 4>> homes;
+        struct Place {
+            uint64_t hi, lo;  // (place among homes, block z), (block y, x, axis)
+            uint32_t cell;
+            bool operator<(const Place& o) const { return std::tie(hi, lo, cell) < std::tie(o.hi, o.lo, o.cell); }
+        };
+        std::vector<Place> place(cells.size());
         for (size_t t = 0; t < cells.size(); ++t) {
             const Cell& c = cells[t];
             auto face = [&](int d) { return c.key[d] < lo[d] + 2 ? 1 : (c.key[d] > hi[d] - 2 ? 2 : 0); };
             // axis of the slab (-1: none) and its side
             const int ax = face(2) ? 2 : (face(1) ? 1 : (face(0) ? 0 : -1));
             const int shape = ax == 1 ? 1 : (ax == 0 ? 2 : 0);
-            std::array<int, 8> id;
-            id[0] = c.q0;
-            for (int d = 0; d < 3; ++d) {
-                id[1 + d] = c.cw[d] - c.key[d];
-                id[4 + d] = (c.key[2 - d] - lo[2 - d]) / brick_dim(R, shape, 2 - d);
+            const std::array<int, 4> home = {c.q0, c.cw[0] - c.key[0], c.cw[1] - c.key[1], c.cw[2] - c.key[2]};
+            size_t h = t > 0 ? place[t - 1].hi >> 32 : 0;
+            if (h >= homes.size() || homes[h] != home) {
+                h = std::find(homes.begin(), homes.end(), home) - homes.begin();
+                if (h == homes.size()) homes.push_back(home);
             }
-            // the two layers of a high face share a block whatever its alignment
-            if (ax >= 0) id[4 + (2 - ax)] = face(ax);
-            id[7] = 4 * ax;
-            blocks[id].push_back(t);
+            uint64_t b[3];
+            for (int d = 0; d < 3; ++d)  // the two layers of a high face share a block whatever its alignment
+                b[d] = d == ax ? face(d) : (c.key[d] - lo[d]) / brick_dim(R, shape, d);
+            place[t] = Place{(uint64_t)h << 32 | b[2], b[1] << 34 | b[0] << 2 | (uint64_t)(ax + 1), (uint32_t)t};
         }
-        for (const auto& bl : blocks) {
+        std::sort(place.begin(), place.end());
+        for (size_t b0 = 0, b1; b0 < place.size(); b0 = b1) {
+            for (b1 = b0; b1 < place.size() && place[b1].hi == place[b0].hi && place[b1].lo == place[b0].lo;) ++b1;
             int k0[3], k1[3];
-            for (int d = 0; d < 3; ++d) k0[d] = k1[d] = cells[bl.second[0]].key[d];
-            for (size_t t : bl.second)
+            for (int d = 0; d < 3; ++d) k0[d] = k1[d] = cells[place[b0].cell].key[d];
+            for (size_t b = b0; b < b1; ++b)
                 for (int d = 0; d < 3; ++d) {
-                    k0[d] = std::min(k0[d], cells[t].key[d]);
-                    k1[d] = std::max(k1[d], cells[t].key[d]);
+                    k0[d] = std::min(k0[d], cells[place[b].cell].key[d]);
+                    k1[d] = std::max(k1[d], cells[place[b].cell].key[d]);
                 }
-            const PatchDev& qd = par.pd[bl.first[0]];
+            const std::array<int, 4>& home = homes[place[b0].hi >> 32];
+            const PatchDev& qd = par.pd[home[0]];
             ProlongBrick e{};
             int c0[3], d0[3];
             for (int d = 0; d < 3; ++d) {
                 e.n[d] = k1[d] - k0[d] + 1;
-                c0[d] = k0[d] + bl.first[1 + d] - qd.lo[d] + G - 2;
+                c0[d] = k0[d] + home[1 + d] - qd.lo[d] + G - 2;
                 d0[d] = R * k0[d] - pd.lo[d] + G;
             }
             e.dbase = pd.off + local_index(pd, d0[0], d0[1], d0[2]);
@@ -444,8 +460,8 @@ struct FineCells {
             e.rows = (int32_t)rows.size();
             const int fy = e.n[1] * R;
             rows.resize(rows.size() + (size_t)fy * e.n[2] * R, 0u);
-            for (size_t t : bl.second) {
-                const Cell& c = cells[t];
+            for (size_t b = b0; b < b1; ++b) {
+                const Cell& c = cells[place[b].cell];
                 for (int mz = 0; mz < R; ++mz)
                     for (int my = 0; my < R; ++my)
                         for (int mx = 0; mx < R; ++mx)
@@ -861,37 +877,42 @@ int build(mol_patchset* ps, const mol_hierarchy_desc* h, const mol_patchset* pre
             std::vector<int64_t> fs_of(par->pd.size());
             for (size_t p = 0; p < lev.pd.size(); ++p) {
                 lev.band_by_patch[p] = (int64_t)band.size();
+                int64_t o0 = par->nelems, o1 = -1;  // range of this patch's points (marked 2)
                 for (int64_t t = pro_by_patch[p]; t < pro_by_patch[p + 1]; ++t) {
                     const ProlongPt& e = pro[t];
                     for (int c = 0; c < (e.m[2] ? 6 : 1); ++c)
                         for (int b = 0; b < (e.m[1] ? 6 : 1); ++b)
                             for (int a = 0; a < (e.m[0] ? 6 : 1); ++a) {
                                 const int64_t o = e.cbase + (int64_t)c * e.cpz + (int64_t)b * e.cpy + a;
-                                if (!mark[o]) {
-                                    mark[o] = 1;
-                                    // global index of this ghosted-box position, and its owner
-                                    const size_t q = (size_t)(std::upper_bound(pstart.begin(), pstart.end(), o) -
-                                                              pstart.begin()) - 1;
-                                    const PatchDev& qd = par->pd[q];
-                                    const int64_t loc = o - qd.off;
-                                    const int lz = (int)(loc / qd.pitch_z), ly = (int)((loc % qd.pitch_z) / qd.pitch_y),
-                                              lx = (int)(loc % qd.pitch_y);
-                                    int g[3] = {qd.lo[0] + lx - G, qd.lo[1] + ly - G, qd.lo[2] + lz - G}, gw[3];
-                                    const int own = find_owner(*par, g, allpar2, gw);
-                                    if (own < 0)
-                                        return fail(MOL_EINVAL, "level %d: prolongation stencil leaves the parent level", l);
-                                    const PatchDev& od = par->pd[own];
-                                    band.push_back(GhostCopy{o,
-                                                             od.off + local_index(od, gw[0] - od.lo[0] + G,
-                                                                                  gw[1] - od.lo[1] + G, gw[2] - od.lo[2] + G),
-                                                             qd.fs, od.fs});
-                                }
+                                if (mark[o]) continue;
+                                mark[o] = 2;
+                                o0 = std::min(o0, o);
+                                o1 = std::max(o1, o);
                             }
                 }
-                // in memory order (found in the order of the ghost points'
-                // stencils), so that a wave's loads share cache lines
-                std::sort(band.begin() + lev.band_by_patch[p], band.end(),
-                          [](const GhostCopy& a, const GhostCopy& b) { return a.src < b.src; });
+                // in memory order, so that a wave's loads share cache lines
+                while (o0 <= o1) {
+                    const void* at = std::memchr(mark.data() + o0, 2, (size_t)(o1 - o0 + 1));
+                    if (!at) break;
+                    const int64_t o = static_cast<const uint8_t*>(at) - mark.data();
+                    o0 = o + 1;
+                    mark[o] = 1;
+                    // global index of this ghosted-box position, and its owner
+                    const size_t q =
+                        (size_t)(std::upper_bound(pstart.begin(), pstart.end(), o) - pstart.begin()) - 1;
+                    const PatchDev& qd = par->pd[q];
+                    const int64_t loc = o - qd.off;
+                    const int lz = (int)(loc / qd.pitch_z), ly = (int)((loc % qd.pitch_z) / qd.pitch_y),
+                              lx = (int)(loc % qd.pitch_y);
+                    int g[3] = {qd.lo[0] + lx - G, qd.lo[1] + ly - G, qd.lo[2] + lz - G}, gw[3];
+                    const int own = find_owner(*par, g, allpar2, gw);
+                    if (own < 0) return fail(MOL_EINVAL, "level %d: prolongation stencil leaves the parent level", l);
+                    const PatchDev& od = par->pd[own];
+                    band.push_back(GhostCopy{o,
+                                             od.off + local_index(od, gw[0] - od.lo[0] + G, gw[1] - od.lo[1] + G,
+                                                                  gw[2] - od.lo[2] + G),
+                                             qd.fs, od.fs});
+                }
             }
             lev.band_by_patch[lev.pd.size()] = (int64_t)band.size();
             if ((rc = lev.band.upload(band, &ps->arena))) return rc;
@@ -2034,6 +2055,7 @@ int mol_regrid_create(mol_patchset* pn, const mol_patchset* po, mol_regrid** out
     if (!r) return fail(MOL_ENOMEM, "host allocation failed");
     r->pn = pn;
     r->po = po;
+    int rc;
     for (int l = 1; l < pn->nlev; ++l) {
         const Level& lev = pn->L[l];
         const Level& old = po->L[l];
@@ -2086,11 +2108,16 @@ int mol_regrid_create(mol_patchset* pn, const mol_patchset* po, mol_regrid** out
                     }
             fc.bricks(pd, par, R, bricks, rows);
         }
-        int rc;
-        if ((rc = r->copy[l].upload(copy)) || (rc = r->bricks[l].upload(bricks)) || (rc = r->rows[l].upload(rows))) {
+        if ((rc = r->copy[l].upload(copy))) {
             delete r;
             return rc;
         }
+        r->bricks[l].upload(bricks, &r->arena);
+        r->rows[l].upload(rows, &r->arena);
+    }
+    if ((rc = r->arena.commit())) {
+        delete r;
+        return rc;
     }
     *out = r;
     return MOL_OK;
