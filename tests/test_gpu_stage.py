@@ -520,3 +520,30 @@ def test_mhd_cell_and_interface_kernels_agree(ny, tiles, system, recon, q):
             ref = _oracle_steps(osys, scheme, synth.embed(st0), dx, 0.1 * dx, 1, prm)
             e = parity_err(out[1], synth.interior(ref))
             assert np.all(e <= TOL), e
+
+
+@pytest.mark.parametrize("upwind", [1, 0])
+def test_ccz4_stage_instances_agree_on_a_ragged_level(upwind):
+    """The CCZ4 stage kernel loads every halo slot on launches of at most 256
+    tiles and masks the unread ones beyond: a level of four ragged patches (200
+    tiles each, 800 together) stepped patch by patch and in one launch, bit for
+    bit, and against the oracle (one RK4 step)."""
+    torch = _torch()
+    n = (66, 50, 37)
+    print("ccz4 instances", n, upwind, flush=True)
+    st0, dx = _ccz4_state(n, "strong")
+    boxes = [((i, j, 0), (i + 32, j + 24, 36)) for j in (0, 25) for i in (0, 33)]
+    ps = M.Patchset(M.Hierarchy(n, (0, 0, 0), dx, [(1, boxes)]), M.System(M.MOL_CCZ4, upwind=upwind))
+    parts = [synth.embed(np.ascontiguousarray(st0[:, :, lo[1]:hi[1] + 1, lo[0]:hi[0] + 1])) for lo, hi in boxes]
+    out = []
+    for mode in (M.MOL_BATCHED, M.MOL_PLAIN):
+        st = ps.alloc_states()
+        st[0]["U"].copy_(torch.from_numpy(ps.pack(0, parts)))
+        ps.advance(st, 0.25 * dx, mode)
+        torch.cuda.synchronize()
+        out.append([synth.interior(a) for a in ps.unpack(0, st[0]["U"])])
+    ref = synth.interior(_oracle_steps(O.CCZ4, O.RK4, synth.embed(st0), dx, 0.25 * dx, 1, O.params(upwind=float(upwind))))
+    for (lo, hi), a, b in zip(boxes, *out):
+        assert np.array_equal(a, b)
+        e = parity_err(a, ref[:, :, lo[1]:hi[1] + 1, lo[0]:hi[0] + 1])
+        assert np.all(e <= TOL), e
