@@ -467,7 +467,9 @@ void mol_regrid_destroy(mol_regrid* r);
 
 /* ---- autotuning of the stage launches ---- */
 typedef struct {
-    int tdim[3]; /* launch shape: thread tile, or 64 x 8 (wave) / 15 x 15 (MHD) columns and a z-chunk length */
+    int tdim[3]; /* launch shape: thread tile, or 64 x 8 (wave) columns and a z-chunk length;
+                    MHD: 15 x 15 and a z-chunk length, whatever columns the level's kernel
+                    owns (LLF and HLL: 14 x 16 on most levels) */
     int order;   /* tiles in the launch: 0 patches as listed, x fastest within a patch;
                     1 largest interior first; 2 as 0 with the tiles of each patch in
                     columns along z (z fastest); 3 as 2 with columns in blocks of 2 x 2 */

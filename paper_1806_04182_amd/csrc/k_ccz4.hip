@@ -375,9 +375,12 @@ __device__ __forceinline__ void ccz4_tile(const StageArgs& a, const CczConst& C,
         constexpr int f = decltype(fc)::value;
         const double* src = a.Us + hbase + (int64_t)f * fs;
         const int wbase = tid & ~63;  // first chunk of this wave's window of 64
+        // fields of which only the cross is read (the monitors differentiate
+        // twice the metric and chi only)
+        constexpr bool cross = !ALL && (MON ? !(f >= GT && f < GT + 6) && f != CHI : single_axis(f));
 #pragma unroll
         for (int r = 0; r < L::NI; ++r)
-            if (!ALL && (MON ? !(f >= GT && f < GT + 6) && f != CHI : single_axis(f)) ? ndx[r] : (r + 1) * NT <= L::NCH || r * NT + tid < L::NCH)
+            if (cross ? ndx[r] : (r + 1) * NT <= L::NCH || r * NT + tid < L::NCH)
                 __builtin_amdgcn_global_load_lds((const void*)(src + doff[r]), (lds_void*)(dst + 2 * (r * NT + wbase)),
                                                  16, 0, 0);
     };
@@ -867,8 +870,9 @@ __global__ __launch_bounds__(TX * TY * TZ, MOL_CCZ4_WAVES) void ccz4_stage_kerne
 // Monitors of a CCZ4 level: the workgroups of an XCD walk its contiguous range
 // of the tile list; each ends with its block's values in partial (fixed order).
 // The kernel streams the fields through LDS like the stage kernel; one thread
-// per point with direct loads of every stencil took 464 registers and 504 us
-// on 101 x 58 x 77 points, this 102 us.
+// per point with direct loads of every stencil took 464 registers: the whole
+// call, all monitors with their point-wise output, on 101 x 58 x 77 points in
+// eight patches 538 us, now 131.
 __global__ __launch_bounds__(256, 2) void ccz4_monitor_kernel(StageArgs a, CczConst C, MonSink init, double* partial)
 {
     constexpr int TX = MOL_CCZ4_TX, TY = MOL_CCZ4_TY, TZ = MOL_CCZ4_TZ;

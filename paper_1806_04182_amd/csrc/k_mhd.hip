@@ -188,8 +188,8 @@ __device__ __forceinline__ void split_flux(Get get, int d, const MhdConst& C, do
 // denominators with the candidates do (WENO5-Z at jumps of any shape: from
 // 10^22.3 without K to 10^22.8); K costs no operation.  eps4 = 4 eps (WENO3: eps).
 template <int REC, bool Q2>
-__device__ __forceinline__ void cell_states(double v0, double v1, double v2, double v3, double v4, double eps4, double q,
-                                            double& left, double& right)
+__device__ __forceinline__ void cell_states(double v0, double v1, double v2, double v3, double v4, double eps4,
+                                            double q, double& left, double& right)
 {
     const double d12 = v2 - v1, d23 = v3 - v2;
     if constexpr (REC == REC_W3) {
@@ -391,8 +391,7 @@ __global__ __launch_bounds__(256, REC == REC_W3 ? 2 : 1) void mhd_cells_kernel(S
         {
             double UL[NF], UR[NF];
 #pragma unroll
-            for (int f = 0; f < NF; ++f)
-{
+            for (int f = 0; f < NF; ++f) {
                 cell_states<REC, Q2>(w[f][0], w[f][1], w[f][2], w[f][3], w[f][4], es, C.q, UL[f], UR[f]);
                 if (f % 2) __builtin_amdgcn_sched_barrier(0);
             }
@@ -441,8 +440,8 @@ __global__ __launch_bounds__(256, REC == REC_W3 ? 2 : 1) void mhd_cells_kernel(S
 #pragma unroll
             for (int f = 0; f < NF; ++f) {
                 const double* p = &pl[b][f][yr + H][yc + H];
-                cell_states<REC, Q2>(TWO ? p[-2 * CHX] : 0.0, p[-CHX], p[0], p[CHX], TWO ? p[2 * CHX] : 0.0, es, C.q, UL[f],
-                                     UR[f]);
+                cell_states<REC, Q2>(TWO ? p[-2 * CHX] : 0.0, p[-CHX], p[0], p[CHX], TWO ? p[2 * CHX] : 0.0, es, C.q,
+                                     UL[f], UR[f]);
                 ey[f][yr + 1][yc] = UR[f];
                 if (f % 2) __builtin_amdgcn_sched_barrier(0);
             }
