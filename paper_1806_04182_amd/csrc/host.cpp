@@ -1158,7 +1158,7 @@ int stage_impl(mol_patchset* ps, int level, int mode, int stage, double dt, cons
     a.stream = lev.nelems * (int64_t)sizeof(double) >= (int64_t(128) << 20);
     a.wrap = wrap ? 1 : 0;
     a.swap = swap ? 1 : 0;
-    a.mhd_cells = lev.tiles.cells ? 1 : 0;
+    sp.mhd_cells = lev.tiles.cells;
     a.images = images ? 1 : 0;
     if (!plain) {
         a.tiles = lev.tiles.dev.p;

@@ -590,7 +590,7 @@ void launch(const SysParams& sp, const StageArgs& a, const MhdConst& C, int zc, 
     const bool hll = sp.mhd_flux == MOL_FLUX_HLL;
     if (sp.mhd_flux == MOL_FLUX_SPLIT)
         go(mhd_faces_kernel<NF, REC, RS_SPLIT, Q2>);
-    else if (a.mhd_cells)
+    else if (sp.mhd_cells)
         hll ? go(mhd_cells_kernel<NF, REC, RS_HLL, Q2>) : go(mhd_cells_kernel<NF, REC, RS_LLF, Q2>);
     else if constexpr ((NF == 8 || REC == REC_W3) && Q2)
         hll ? go(mhd_faces_kernel<NF, REC, RS_HLL, Q2>) : go(mhd_faces_kernel<NF, REC, RS_LLF, Q2>);

@@ -144,6 +144,9 @@ struct SysParams {
     double sigma, gamma_ad, weno_eps, weno_q, kappa_z, kappa_c, bm_f0, bm_f1, gd_g, gd_eta;
     int mhd_recon, mhd_flux;
     double mhd_ch, mhd_kpsi;
+    // the level's MHD stage tiles cover MHD_CX x MHD_CY columns (the cell
+    // kernel) rather than 15 x 15 (the interface kernel)
+    bool mhd_cells = false;
 };
 
 // What the fused stage kernels do after evaluating k = dt * rhs.
@@ -174,9 +177,6 @@ struct StageArgs {
     // stencils are symmetric, so d_t (Pi, phi) of the transpose is the forward
     // right-hand side)
     int swap;
-    // 1 when the tiles of an MHD level cover MHD_CX x MHD_CY columns (the cell
-    // kernel), 0 when they cover 15 x 15 (the interface kernel)
-    int mhd_cells;
     // 1 when the driver steps a CCZ4 level that is one periodic patch of at
     // least 2G points per axis: the stage kernel also writes its output at
     // the periodic ghost images of every point within G of a face (faces,
