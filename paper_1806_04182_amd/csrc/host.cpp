@@ -571,9 +571,9 @@ int build_tiles(const Level& lev, const int shape[3], int margin, TileList& tl, 
 // rounds of 256 workgroups (one per compute unit; two for WENO3, whose kernel
 // fits two) times the planes of a chunk and its lead-in (two z
 // reconstructions, 0.7 of a plane; interface kernel: one z flux, whose loads
-// the first plane shares, 0.1).  Measured at 128^3 (WENO5-Z, LLF) 393 us with chunks
-// of 8 (cost 43), 424 with 4 (47), 445 with 16 (50), 487 with 2 (54); at 32^3 24
-// us with 2 and 40 with 4.  Flux splitting takes chunks of 4 within 2.5% of the
+// the first plane shares, 0.1).  Measured at 128^3 (WENO5-Z, LLF, SSP-RK3 stage)
+// 393 us with chunks of 8 (cost 43), 424 with 4 (47), 445 with 16 (50), 487 with 2
+// (54); at 32^3 24 us with 2 and 40 with 4.  Flux splitting takes chunks of 4 within 2.5% of the
 // lowest cost, since many rounds even out tiles of few columns (WENO3, 27
 // patches of 32^3 571 us with 4, 608 with 32; 8 of 36^3 196 and 204 with 12; 8
 // of 48^3 432 and 444 with 24), except for one chunk per patch of up to 24

@@ -314,10 +314,11 @@ constexpr int DPP_FROM_NEXT = 0x101, DPP_FROM_PREV = 0x111;  // row_shl:1, row_s
 // plane ahead.  Why cells instead of interfaces: the kernel is bound by FP64
 // issue, and the indicators, most of the reconstruction's arithmetic, are the
 // same for both states of a cell.  Interface by interface before, this after
-// (128^3 stage): WENO5-Z 0.557 -> 0.393 ms, WENO5-JS 0.524 -> 0.380, WENO3 with
-// HLL 0.412 -> 0.250; a sixth of it from requesting a point's stage inputs
-// together (0.488 -> 0.409) and a further 4% from two barriers per plane
-// instead of four.
+// (128^3, rough data, LLF; HLL within 2%): SSP-RK3 stage WENO5-Z 0.597 -> 0.397
+// ms, WENO5-JS 0.565 -> 0.385, WENO3 0.433 -> 0.276; RK4 stage, five arrays
+// instead of three, 0.641 -> 0.433, 0.614 -> 0.421 and 0.484 -> 0.301.  A sixth
+// of it came from requesting a point's stage inputs together and a further 4%
+// from two barriers per plane instead of four.
 // The scheduling barriers keep two fields' reconstructions in flight at a
 // time: without them the kernel spills.  The WENO5 instances take more than
 // 256 registers and run one wave per SIMD without scratch (held to two waves
